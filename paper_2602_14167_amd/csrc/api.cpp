@@ -1911,7 +1911,7 @@ tcng_status multi_build(const tcng_circuit* const* circs, const tcng_pauli_sum* 
         F.n_gates = int32_t(c->gates.size());
         F.erows = Li.e_rows;
         M.fins[i] = F;
-        M.fprefix[i + 1] = M.fprefix[i] + 1 + c->n_params + (F.gate_grad ? int64_t(c->gates.size()) : 0);
+        M.fprefix[i + 1] = M.fprefix[i] + 1 + c->n_params + (F.gate_grad ? GATE_OUTS * int64_t(c->gates.size()) : 0);
     }
     if (L.fused) {
         M.fjobs.resize(count);

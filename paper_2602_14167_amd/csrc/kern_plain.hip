@@ -395,23 +395,44 @@ __global__ void k_zero(double* __restrict__ p, size_t count) {
         p[i] = 0.0;
 }
 
-// row sums of the per-workgroup partials: one wave per row, lanes stride the
-// row, then a butterfly (fixed order: deterministic)
-__global__ void __launch_bounds__(256) k_rowsum(const double* __restrict__ in, int64_t rows, int len,
-                                                double* __restrict__ out) {
-    const int64_t row = int64_t(blockIdx.x) * 4 + (threadIdx.x >> 6);
+// row sums of the per-workgroup partials of two tables in one launch (gradient
+// slots, then energy rows): one wave per row, lanes stride the row, then a
+// butterfly (fixed order: deterministic).  A row is a serial chain of loads per
+// lane unless several are in flight: 8 at a time took the longest rows (8192
+// partials, 28 qubits) from 53 us.
+struct RowTable {
+    const double* in;
+    double* out;
+    int64_t rows;
+    int len;
+};
+__global__ void __launch_bounds__(256) k_rowsum(const RowTable a, const RowTable b) {
+    int64_t row = int64_t(blockIdx.x) * 4 + (threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
-    if (row >= rows) return;   // whole wave leaves together
-    const double* p = in + size_t(row) * len;
+    if (row >= a.rows + b.rows) return;   // whole wave leaves together
+    const bool second = row >= a.rows;
+    if (second) row -= a.rows;
+    const int len = second ? b.len : a.len;
+    const double* p = (second ? b.in : a.in) + size_t(row) * len;
     double v = 0.0;
-    for (int i = lane; i < len; i += 64) v += p[i];
+    int i = lane;
+    for (; i + 7 * 64 < len; i += 8 * 64) {
+        double x[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) x[k] = p[i + 64 * k];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) v += x[k];
+    }
+    for (; i < len; i += 64) v += p[i];
     v = wave_sum(v);
-    if (lane == 0) out[row] = v;
+    if (lane == 0) (second ? b.out : a.out)[row] = v;
 }
 
 // final sums: one thread per (member, output), fixed order everywhere
-// output k of one circuit: k = 0 energy, 1..n_params gradient, then one
-// 15-vector of Lie-algebra derivatives per gate (when gate_grad is wanted)
+// output k of one circuit: k = 0 energy, 1..n_params gradient, then 16 per gate
+// (when gate_grad is wanted): its 15 Lie-algebra derivatives and one idle
+// (one thread per gate left most of a wave's work to 15 serial traces: 171 us
+// for 60 circuits of 12 to 20 qubits)
 __device__ void finish_one(const FinishJob& F, int64_t k) {
     const double* sl = F.slots;
     if (k == 0) {
@@ -425,11 +446,13 @@ __device__ void finish_one(const FinishJob& F, int64_t k) {
         F.grad[p] = g;
     } else {
         // per U2 gate: dE/dalpha_k = Im tr(G^dag P_k U), P_k = sigma_a (x) sigma_b, k = 4a + b - 1
-        const int gi = int(k - 1 - F.n_params);
+        const int64_t r = k - 1 - F.n_params;
+        const int gi = int(r / GATE_OUTS), kk = int(r % GATE_OUTS);
+        if (kk == 15) return;
         double* out = F.gate_grad + size_t(gi) * 15;
         const int s0 = F.gate_slot[gi];
         if (s0 < 0) {
-            for (int i = 0; i < 15; ++i) out[i] = 0.0;
+            out[kk] = 0.0;
             return;
         }
         const double* U = F.u2m + size_t(F.gate_mat[gi]) * 32;
@@ -441,28 +464,26 @@ __device__ void finish_one(const FinishJob& F, int64_t k) {
             else if (a == 2) im = (r == c) ? 0.0 : (r == 0 ? -1.0 : 1.0);
             else re = (r == c) ? (r == 0 ? 1.0 : -1.0) : 0.0;
         };
-        for (int kk = 0; kk < 15; ++kk) {
-            const int a = (kk + 1) >> 2, c = (kk + 1) & 3;
-            double tr_im = 0.0;
-            for (int x = 0; x < 4; ++x)
-                for (int y = 0; y < 4; ++y) {
-                    // (P U)[y][x] = sum_z P[y][z] U[z][x]
-                    double pur = 0.0, pui = 0.0;
-                    for (int z = 0; z < 4; ++z) {
-                        double s1r, s1i, s2r, s2i;
-                        sig(a, y >> 1, z >> 1, s1r, s1i);
-                        sig(c, y & 1, z & 1, s2r, s2i);
-                        const double pr = s1r * s2r - s1i * s2i, pi = s1r * s2i + s1i * s2r;
-                        const double ur = U[2 * (4 * z + x)], ui = U[2 * (4 * z + x) + 1];
-                        pur += pr * ur - pi * ui;
-                        pui += pr * ui + pi * ur;
-                    }
-                    // conj(G[y][x]) * (PU)[y][x]
-                    const double gr = sl[s0 + 2 * (4 * y + x)], gim = sl[s0 + 2 * (4 * y + x) + 1];
-                    tr_im += gr * pui - gim * pur;
+        const int a = (kk + 1) >> 2, c = (kk + 1) & 3;
+        double tr_im = 0.0;
+        for (int x = 0; x < 4; ++x)
+            for (int y = 0; y < 4; ++y) {
+                // (P U)[y][x] = sum_z P[y][z] U[z][x]
+                double pur = 0.0, pui = 0.0;
+                for (int z = 0; z < 4; ++z) {
+                    double s1r, s1i, s2r, s2i;
+                    sig(a, y >> 1, z >> 1, s1r, s1i);
+                    sig(c, y & 1, z & 1, s2r, s2i);
+                    const double pr = s1r * s2r - s1i * s2i, pi = s1r * s2i + s1i * s2r;
+                    const double ur = U[2 * (4 * z + x)], ui = U[2 * (4 * z + x) + 1];
+                    pur += pr * ur - pi * ui;
+                    pui += pr * ui + pi * ur;
                 }
-            out[kk] = tr_im;
-        }
+                // conj(G[y][x]) * (PU)[y][x]
+                const double gr = sl[s0 + 2 * (4 * y + x)], gim = sl[s0 + 2 * (4 * y + x) + 1];
+                tr_im += gr * pui - gim * pur;
+            }
+        out[kk] = tr_im;
     }
 }
 
@@ -471,7 +492,7 @@ __global__ void k_finish(const double* __restrict__ slots, int total_slots, cons
                          int erows, int64_t batch, double* __restrict__ energy, double* __restrict__ grad,
                          double* __restrict__ gate_grad, const int32_t* __restrict__ gate_slot,
                          const double* __restrict__ u2m, const int32_t* __restrict__ gate_mat, int n_gates) {
-    const int64_t per = int64_t(1) + n_params + (gate_grad ? int64_t(n_gates) : 0);
+    const int64_t per = int64_t(1) + n_params + (gate_grad ? GATE_OUTS * int64_t(n_gates) : 0);
     const int64_t tid = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
     if (tid >= per * batch) return;
     const int64_t b = tid / per;
@@ -890,6 +911,13 @@ hipError_t launch_zero(double* p, size_t count, hipStream_t st) {
     return hipGetLastError();
 }
 
+static hipError_t launch_rowsum(const RowTable& a, const RowTable& b, hipStream_t st) {
+    const int64_t rows = a.rows + b.rows;
+    if (rows <= 0) return hipSuccess;
+    hipLaunchKernelGGL(k_rowsum, dim3(unsigned((rows + 3) / 4)), dim3(256), 0, st, a, b);
+    return hipGetLastError();
+}
+
 hipError_t launch_finish(const double* part, int total_slots, int wgs, const int32_t* slot_ptr,
                          const int32_t* slot_idx, int n_params, const double* epart, int erows, int ewgs,
                          int64_t batch, double* energy, double* grad, double* gate_grad, const int32_t* gate_slot,
@@ -898,16 +926,10 @@ hipError_t launch_finish(const double* part, int total_slots, int wgs, const int
     // scratch: [batch][total_slots] slot sums, then [batch][erows] energy row sums
     double* slots = scratch;
     double* erow = scratch + size_t(batch) * total_slots;
-    const int64_t srows = batch * int64_t(total_slots), er = batch * int64_t(erows);
-    if (srows > 0 && part) {
-        hipLaunchKernelGGL(k_rowsum, dim3(unsigned((srows + 3) / 4)), dim3(256), 0, st, part, srows, wgs, slots);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
-    hipLaunchKernelGGL(k_rowsum, dim3(unsigned((er + 3) / 4)), dim3(256), 0, st, epart, er, ewgs, erow);
-    hipError_t e = hipGetLastError();
+    const int64_t srows = part ? batch * int64_t(total_slots) : 0, er = batch * int64_t(erows);
+    hipError_t e = launch_rowsum({part, slots, srows, wgs}, {epart, erow, er, ewgs}, st);
     if (e != hipSuccess) return e;
-    const int64_t per = 1 + n_params + (gate_grad ? n_gates : 0);
+    const int64_t per = 1 + n_params + (gate_grad ? GATE_OUTS * int64_t(n_gates) : 0);
     const int64_t work = per * batch;
     hipLaunchKernelGGL(k_finish, dim3(unsigned((work + 255) / 256)), dim3(256), 0, st, slots, total_slots, slot_ptr,
                        slot_idx, n_params, erow, erows, batch, energy, grad, gate_grad, gate_slot, u2_mats_c128,
@@ -918,17 +940,8 @@ hipError_t launch_finish(const double* part, int total_slots, int wgs, const int
 hipError_t launch_finish_multi(const double* part, int64_t prows, int wgs, const double* epart, int64_t erows_total,
                                int ewgs, double* slot_sums, double* erow_sums, const FinishJob* jobs,
                                const int64_t* prefix, int njobs, int64_t total, hipStream_t st) {
-    if (prows > 0) {
-        hipLaunchKernelGGL(k_rowsum, dim3(unsigned((prows + 3) / 4)), dim3(256), 0, st, part, prows, wgs, slot_sums);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
-    if (erows_total > 0) {
-        hipLaunchKernelGGL(k_rowsum, dim3(unsigned((erows_total + 3) / 4)), dim3(256), 0, st, epart, erows_total, ewgs,
-                           erow_sums);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
+    hipError_t e = launch_rowsum({part, slot_sums, prows, wgs}, {epart, erow_sums, erows_total, ewgs}, st);
+    if (e != hipSuccess) return e;
     if (total <= 0) return hipSuccess;
     hipLaunchKernelGGL(k_finish_multi, dim3(unsigned((total + 255) / 256)), dim3(256), 0, st, jobs, prefix, njobs,
                        total);

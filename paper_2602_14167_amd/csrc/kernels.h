@@ -228,6 +228,7 @@ struct BuildJob {
     void* opm;
     int32_t n_ops, pad;
 };
+constexpr int GATE_OUTS = 16;   // outputs k_finish numbers per gate (15 derivatives, one idle)
 struct FinishJob {
     const double* slots;      // row sums of this circuit's gradient partials
     const double* erow;       // row sums of its energy partials
@@ -244,7 +245,7 @@ struct FinishJob {
 template <typename R>
 hipError_t launch_build_ops_multi(const BuildJob* jobs, const int64_t* prefix, int njobs, int64_t total,
                                   hipStream_t st);
-// prefix[j]: first output thread of job j (outputs: energy, n_params gradients, n_gates gate rows if gate_grad)
+// prefix[j]: first output thread of job j (outputs: energy, n_params gradients, GATE_OUTS per gate if gate_grad)
 hipError_t launch_finish_multi(const double* part, int64_t prows, int wgs, const double* epart, int64_t erows_total,
                                int ewgs, double* slot_sums, double* erow_sums, const FinishJob* jobs,
                                const int64_t* prefix, int njobs, int64_t total, hipStream_t st);

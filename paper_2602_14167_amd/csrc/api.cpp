@@ -1570,7 +1570,7 @@ tcng_status tcng_mipt_run(const tcng_circuit* step, int32_t n_steps, const void*
                                                            M.wgs, st));
         // the measured qubits in rounds of up to 8: one histogram read and the decisions
         // each; rounds after the first visit only the members their predecessor listed
-        PROF_TRY(F_MIPT_DECIDE, launch_mipt_lists_reset(lists, n, batch, st));
+        // (round 0's read clears the lists)
         for (int r = 0; r < mipt_rounds(n); ++r) {
             PROF_TRY(F_MIPT_HIST,
                      launch_mipt_hist(psi->amps, psi->stride, n, batch, u, n_steps, s, p, r, rec, part, lists, st));

@@ -40,19 +40,21 @@ constexpr int HK = 8;                 // measured qubits per histogram round
 constexpr int HBINS = 1 << HK;
 constexpr int HCHUNK = 13;            // amplitudes per histogram workgroup: at most 2^13
 
-__device__ __forceinline__ bool measures(const double* u, int64_t b, int n_steps, int s, int n, int q, double p) {
-    return u[(b * n_steps + s) * n + q] >= 1.0 - p;
+// the qubits member b measures in step s, from one load per lane (n <= 34 lanes;
+// called by whole waves): a serial walk over the uniforms cost a load's
+// latency per qubit, 10 us of a 20-qubit decision
+__device__ __forceinline__ uint32_t measured_mask(const double* u, int64_t b, int n_steps, int s, int n, double p) {
+    const int lane = threadIdx.x & 63;
+    const bool hit = lane < n && u[(b * n_steps + s) * n + lane] >= 1.0 - p;
+    return uint32_t(__ballot(hit));
 }
 
-// the qubits member b measures in step s with rank [r HK, (r + 1) HK) among them
-__device__ __forceinline__ uint32_t round_mask(const double* u, int64_t b, int n_steps, int s, int n, double p, int r) {
+// those of rank [r HK, (r + 1) HK) among them
+__device__ __forceinline__ uint32_t round_mask(uint32_t all, int r) {
     uint32_t m = 0;
     int c = 0;
-    for (int q = 0; q < n; ++q)
-        if (u[(b * n_steps + s) * n + q] >= 1.0 - p) {
-            if (c >= r * HK && c < (r + 1) * HK) m |= 1u << q;
-            ++c;
-        }
+    for (uint32_t mk = all; mk; mk &= mk - 1, ++c)
+        if (c >= r * HK && c < (r + 1) * HK) m |= mk & (0u - mk);
     return m;
 }
 
@@ -72,7 +74,7 @@ __device__ __forceinline__ void hist_member(const float4* __restrict__ psi, int6
                                             const double* __restrict__ u, int n_steps, int s, double p, int r,
                                             const uint32_t* __restrict__ rec, int wgs, double* __restrict__ part,
                                             int64_t b, int wg, float* w2, double* red) {
-    const uint32_t M = round_mask(u, b, n_steps, s, n, p, r);
+    const uint32_t M = round_mask(measured_mask(u, b, n_steps, s, n, p), r);
     if (!M) return;
     const uint32_t md = rec[(b * n_steps + s) * 2], bd = rec[(b * n_steps + s) * 2 + 1];
     const uint32_t A = (1u << n) / uint32_t(wgs);   // amplitudes of the chunk (<= 2^HCHUNK)
@@ -150,10 +152,15 @@ __global__ void __launch_bounds__(MTHREADS) k_mipt_hist(const float4* __restrict
                                                         const double* __restrict__ u, int n_steps, int s, double p,
                                                         int r, const uint32_t* __restrict__ rec, int wgs,
                                                         double* __restrict__ part, const uint32_t* __restrict__ list,
-                                                        const uint32_t* __restrict__ cnt) {
+                                                        const uint32_t* __restrict__ cnt, uint32_t* __restrict__ reset,
+                                                        int rounds, size_t reset_stride) {
     __shared__ float w2[1 << HCHUNK];
     __shared__ double red[MTHREADS / 64];
     if (!list) {
+        // the later rounds' list counters, before this round's decisions append to them
+        // (the previous step's rounds, which read them, are complete)
+        if (reset && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x >= 1 && int(threadIdx.x) < rounds)
+            reset[threadIdx.x * reset_stride] = 0u;
         hist_member(psi, stride4, n, u, n_steps, s, p, r, rec, wgs, part, blockIdx.y, blockIdx.x, w2, red);
         return;
     }
@@ -173,23 +180,45 @@ __device__ __forceinline__ void decide_member(const double* __restrict__ u, int 
                                               uint32_t* __restrict__ list_next, uint32_t* __restrict__ cnt_next,
                                               int64_t b, double* H) {
     const int lane = threadIdx.x;
-    const uint32_t M = round_mask(u, b, n_steps, s, n, p, r);
+    const uint32_t all = measured_mask(u, b, n_steps, s, n, p);
+    const uint32_t M = round_mask(all, r);
     if (!M) return;
     const int K = __popc(M);
     const uint32_t A = (1u << n) / uint32_t(wgs);
     const uint32_t mloc = M & (A - 1), mhigh = M & ~(A - 1);
     const int kloc = __popc(mloc);
-    // bin g: low kloc bits from inside a chunk, the rest from the chunk's base
+    // bin g: low kloc bits from inside a chunk, the rest from the chunk's base; its
+    // chunks w (the bits of w outside mhigh run free) in increasing order, 8
+    // partials in flight (one at a time, a decision took 55 us at 20 qubits)
+    const uint32_t whigh = mhigh / A, wfree = (uint32_t(wgs) - 1u) & ~whigh;
+    const int nw = 1 << __popc(wfree);
     for (int g = lane; g < (1 << K); g += 64) {
-        const uint32_t lo = uint32_t(g) & ((1u << kloc) - 1), hi = deposit(uint32_t(g) >> kloc, mhigh);
+        const uint32_t lo = uint32_t(g) & ((1u << kloc) - 1), hi = deposit(uint32_t(g) >> kloc, mhigh) / A;
+        const double* src = part + (size_t(b) * wgs + hi) * HBINS + lo;
         double t = 0.0;
-        for (int w = 0; w < wgs; ++w)
-            if (((uint32_t(w) * A) & mhigh) == hi) t += part[(size_t(b) * wgs + w) * HBINS + lo];
+        uint32_t w = 0;   // the free bits, counted up through wfree
+        int k = 0;
+        for (; k + 8 <= nw; k += 8) {
+            double x[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                x[j] = src[size_t(w) * HBINS];
+                w = ((w | ~wfree) + 1u) & wfree;
+            }
+#pragma unroll
+            for (int j = 0; j < 8; ++j) t += x[j];
+        }
+        for (; k < nw; ++k) {
+            t += src[size_t(w) * HBINS];
+            w = ((w | ~wfree) + 1u) & wfree;
+        }
         H[g] = t;
     }
+    const double my_u = lane < n ? u[(b * n_steps + s) * n + lane] : 0.0;   // the uniform of qubit `lane`
     __syncthreads();
     uint32_t* rc = rec + (b * n_steps + s) * 2;
     uint32_t dm = 0, db = 0;   // decided bits (bin positions) and their values
+    uint32_t rbits = 0;        // outcomes by qubit
     double lp = 0.0, kp = 0.0;
     int i = 0;
     for (uint32_t mk = M; mk; mk &= mk - 1, ++i) {
@@ -202,7 +231,7 @@ __device__ __forceinline__ void decide_member(const double* __restrict__ u, int 
         }
         s0 = wave_sum(s0);
         s1 = wave_sum(s1);
-        const double v = u[(b * n_steps + s) * n + q];
+        const double v = __shfl(my_u, q, 64);
         const double tot = s0 + s1;
         const double mg = (v - (1.0 - p)) - p * (s0 / tot);
         const int o = mg < 0.0 ? 0 : 1;
@@ -210,18 +239,17 @@ __device__ __forceinline__ void decide_member(const double* __restrict__ u, int 
         lp += log(kp / tot);
         dm |= 1u << i;
         db |= uint32_t(o) << i;
-        if (lane == 0) {
-            rc[0] |= 1u << q;
-            rc[1] |= uint32_t(o) << q;
-            if (margin) margin[(b * n_steps + s) * n + q] = mg;
-        }
+        rbits |= uint32_t(o) << q;
+        if (margin && lane == 0) margin[(b * n_steps + s) * n + q] = mg;
     }
     if (lane == 0) {
+        rc[0] |= M;
+        rc[1] |= rbits;
         logp[b] += lp;
         keep[b] = kp;
     }
     // members with a qubit in the next round go on its list
-    if (list_next && lane == 0 && round_mask(u, b, n_steps, s, n, p, r + 1) != 0u)
+    if (list_next && lane == 0 && round_mask(all, r + 1) != 0u)
         list_next[atomicAdd(cnt_next, 1u)] = uint32_t(b);
 }
 
@@ -268,10 +296,6 @@ __global__ void __launch_bounds__(MTHREADS) k_mipt_collapse(float4* __restrict__
     }
 }
 
-__global__ void k_reset_counts(uint32_t* lists, int rounds, size_t stride) {
-    if (int(threadIdx.x) < rounds) lists[size_t(threadIdx.x) * stride] = 0u;
-}
-
 __global__ void k_zero_u32(uint32_t* p, size_t count) {
     for (size_t i = size_t(blockIdx.x) * 256 + threadIdx.x; i < count; i += size_t(gridDim.x) * 256) p[i] = 0u;
 }
@@ -293,7 +317,7 @@ size_t mipt_list_words(int n, int64_t batch) { return size_t(mipt_rounds(n)) * (
 static unsigned list_rows(int64_t batch, unsigned cap) { return unsigned(std::min<int64_t>(batch, cap)); }
 
 hipError_t launch_mipt_hist(const void* psi, int64_t stride, int n, int64_t batch, const double* u, int n_steps, int s,
-                            double p, int r, const uint32_t* rec, double* part, const uint32_t* lists,
+                            double p, int r, const uint32_t* rec, double* part, uint32_t* lists,
                             hipStream_t st) {
     if (batch == 0) return hipSuccess;
     if (n < HK) return hipErrorInvalidValue;   // a chunk holds at least one index per thread and bin
@@ -302,7 +326,8 @@ hipError_t launch_mipt_hist(const void* psi, int64_t stride, int n, int64_t batc
     const uint32_t* cnt = r > 0 ? lists + size_t(r) * (batch + 1) : nullptr;
     const unsigned rows = r > 0 ? list_rows(batch, 64) : unsigned(batch);
     hipLaunchKernelGGL(k_mipt_hist, dim3(unsigned(wgs), rows), dim3(MTHREADS), 0, st, static_cast<const float4*>(psi),
-                       stride / 2, n, u, n_steps, s, p, r, rec, wgs, part, list, cnt);
+                       stride / 2, n, u, n_steps, s, p, r, rec, wgs, part, list, cnt, r == 0 ? lists : nullptr,
+                       mipt_rounds(n), size_t(batch) + 1);
     return hipGetLastError();
 }
 
@@ -319,13 +344,6 @@ hipError_t launch_mipt_decide(const double* u, int n, int n_steps, int s, double
     const unsigned rows = r > 0 ? list_rows(batch, 1024) : unsigned(batch);
     hipLaunchKernelGGL(k_mipt_decide, dim3(rows), dim3(64), 0, st, u, n, n_steps, s, p, r, mipt_hist_wgs(n), part,
                        rec, keep, logp, margin, list, cnt, list_next, cnt_next);
-    return hipGetLastError();
-}
-
-// the list counters of rounds 1.. (before a step's round 0)
-hipError_t launch_mipt_lists_reset(uint32_t* lists, int n, int64_t batch, hipStream_t st) {
-    if (batch == 0 || mipt_rounds(n) < 2) return hipSuccess;
-    hipLaunchKernelGGL(k_reset_counts, dim3(1), dim3(64), 0, st, lists, mipt_rounds(n), size_t(batch) + 1);
     return hipGetLastError();
 }
 

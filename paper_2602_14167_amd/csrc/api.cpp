@@ -92,6 +92,14 @@ bool tiled_ok(int n, int dtype) {
     const TileConfig c = tile_config(dtype);
     return n >= std::max(c.rb, c.rb_rev) + 6;
 }
+// states of one workgroup (kern_small.hip)
+bool small_n(int n) { return n >= 2 && n <= SM_QUBITS; }
+// the small-state kernel serves the calls whose state is too small for the
+// tiled plans (a wave's 64 lanes beside the register bits): complex64 to 10
+// qubits, complex128 to 9.  It replaces one launch per gate and sweep.  At 10
+// qubits in complex128 the tiled pass stays: it takes 113 us for one
+// parameter set and gains on larger batches.
+bool use_small(int mode, int n, int dtype) { return mode == TCNG_MODE_TILED && small_n(n) && !tiled_ok(n, dtype); }
 bool config_ok(const TileConfig& c, int dtype) {
     const int mmax = dtype == TCNG_C64 ? 13 : 12;
     const int rbs[2] = {c.rb, c.rb_rev};
@@ -201,6 +209,11 @@ struct tcng_circuit {
     double* u2m[2] = {nullptr, nullptr};       // constant matrices as the run sees them, widened to c128
     int32_t* gate_mat = nullptr;               // [n_gates] matrix index (for gate gradients)
     std::vector<int> plain_slot;               // first slot per gate (plain path), -1 none
+    // small states (2..SM_QUBITS qubits): one allocation holding chunks and gates
+    SChunk* small_tab = nullptr;
+    const SOp* small_ops = nullptr;
+    SChunk small_chunk0{};
+    int small_chunks = 0, small_tab_ops = 0, small_tab_mat = 0;
     SlotTables plain;
     DevCircuitPlan tiled[2];
     DevFusedPlan fused;              // complex64 matrix-core plan (16 x 16 blocks)
@@ -216,6 +229,8 @@ struct tcng_pauli_sum {
     std::vector<PauliTermHost> terms;
     // plain grouping
     std::vector<PGroupFull> groups_full;
+    PGroupFull* groups_dev = nullptr;    // states of one workgroup only
+    int n_classes_full = 0;
     PClassFull* classes_full = nullptr;
     PTermFull* terms_full = nullptr;
     // tiled plans per dtype
@@ -672,6 +687,44 @@ tcng_status run_reverse_fused(const tcng_circuit* c, const void* params, const t
     return TCNG_OK;
 }
 
+// small states: the parts of one evaluation in one launch
+SmallJob small_job(const tcng_circuit* c, const void* params, const tcng_pauli_sum* h, const tcng_state* s, void* lam,
+                   double* energy) {
+    SmallJob J{};
+    J.psi = s->amps;
+    J.lam = lam;
+    J.stride = s->stride;
+    J.n = s->n_qubits;
+    J.energy = energy;
+    if (c) {
+        J.chunks = c->small_tab;
+        J.chunk0 = c->small_chunk0;
+        J.ops = c->small_ops;
+        J.n_chunks = c->small_chunks;
+        J.tab_ops = c->small_tab_ops;
+        J.tab_mat = c->small_tab_mat;
+        J.params = params;
+        J.n_params = c->n_params;
+        J.n_gates = int32_t(c->gates.size());
+        J.cm = c->cm[s->dtype];
+        J.do_fwd = 1;
+    }
+    if (h) {
+        J.groups = h->groups_dev;
+        J.classes = h->classes_full;
+        J.terms = h->terms_full;
+        J.n_groups = J.tab_groups = int32_t(h->groups_full.size());
+        J.tab_classes = h->n_classes_full;
+        J.tab_terms = h->n_terms;
+        J.do_pauli = 1;
+    }
+    return J;
+}
+tcng_status run_small(const SmallJob& J, const tcng_state* s, int family, hipStream_t st) {
+    PROF_TRY(family, s->dtype == TCNG_C64 ? launch_small<float>(J, s->batch, st) : launch_small<double>(J, s->batch, st));
+    return ok();
+}
+
 tcng_status check_circuit_state(const tcng_circuit* c, const tcng_state* s, const void* params) {
     if (!c) return fail(TCNG_E_INVALID, "null circuit");
     if (c->n != s->n_qubits) return fail(TCNG_E_INVALID, "circuit and state have different qubit counts");
@@ -800,6 +853,24 @@ tcng_status tcng_circuit_create(int32_t n_qubits, const tcng_gate* gates, int32_
         if (tcng_status e = build_slot_tables(c->gates, n_params, ptr, idx, gate_slot, total, c->plain))
             return cleanup(e);
     }
+    if (small_n(n_qubits)) {
+        SmallPlan P;
+        plan_small(c->gates, c->plain_slot, P);
+        const size_t oo = sizeof(SChunk) * P.chunks.size();
+        std::vector<unsigned char> tab(oo + sizeof(SOp) * P.ops.size());
+        if (!P.ops.empty()) {
+            std::memcpy(tab.data(), P.chunks.data(), oo);
+            std::memcpy(tab.data() + oo, P.ops.data(), tab.size() - oo);
+            c->small_chunk0 = P.chunks[0];
+        }
+        unsigned char* p = nullptr;
+        if (upload(tab, &p) != hipSuccess) return cleanup(fail(TCNG_E_ALLOC, "device allocation failed"));
+        c->small_tab = reinterpret_cast<SChunk*>(p);
+        c->small_ops = reinterpret_cast<const SOp*>(p + oo);
+        c->small_chunks = int(P.chunks.size());
+        c->small_tab_ops = P.tab_ops;
+        c->small_tab_mat = P.tab_mat;
+    }
     // tiled plans
     for (int dt = 0; dt < 2; ++dt) {
         if (!tiled_ok(n_qubits, dt)) continue;
@@ -825,6 +896,7 @@ tcng_status tcng_circuit_destroy(tcng_circuit* c) {
     (void)hipFree(c->u2m[0]);
     (void)hipFree(c->u2m[1]);
     (void)hipFree(c->gate_mat);
+    (void)hipFree(c->small_tab);
     (void)hipFree(c->plain.ptr);
     (void)hipFree(c->plain.idx);
     (void)hipFree(c->plain.gate_slot);
@@ -902,6 +974,9 @@ tcng_status tcng_pauli_sum_create(int32_t n_qubits, const uint8_t* codes, const 
     std::vector<PClassFull> cls;
     std::vector<PTermFull> tf;
     group_pauli_full(h->terms, h->groups_full, cls, tf);
+    h->n_classes_full = int(cls.size());
+    if (small_n(n_qubits) && upload(h->groups_full, &h->groups_dev) != hipSuccess)
+        return cleanup(fail(TCNG_E_ALLOC, "device allocation failed"));
     if (cls.empty()) cls.push_back(PClassFull{});
     if (tf.empty()) tf.push_back(PTermFull{});
     if (upload(cls, &h->classes_full) != hipSuccess || upload(tf, &h->terms_full) != hipSuccess)
@@ -929,6 +1004,7 @@ tcng_status tcng_pauli_sum_create(int32_t n_qubits, const uint8_t* codes, const 
 tcng_status tcng_pauli_sum_destroy(tcng_pauli_sum* h) {
     if (!h) return ok();
     (void)hipDeviceSynchronize();
+    (void)hipFree(h->groups_dev);
     (void)hipFree(h->classes_full);
     (void)hipFree(h->terms_full);
     (void)hipFree(h->coo_x);
@@ -982,6 +1058,8 @@ tcng_status tcng_run_circuit(const tcng_circuit* c, const void* params, const tc
         const tcng_status e = run_forward_fused(c, params, s, J, false, st, L.fk);
         return e ? e : ok();
     }
+    if (use_small(mode, s->n_qubits, s->dtype))
+        return run_small(small_job(c, params, nullptr, s, nullptr, nullptr), s, F_FWD_TILE, st);
     void* opm = tiled ? static_cast<char*>(ws) + L.opm_off : nullptr;
     const Job J = make_job(c, nullptr, s, nullptr, opm, nullptr, nullptr, L);
     tcng_status e;
@@ -1001,10 +1079,13 @@ tcng_status tcng_expect_pauli(const tcng_state* s, const tcng_pauli_sum* h, doub
     if (!h || !out) return fail(TCNG_E_INVALID, "null Pauli sum or output");
     if (h->n != s->n_qubits) return fail(TCNG_E_INVALID, "Pauli sum and state differ in qubit count");
     if (!valid_mode(mode)) return fail(TCNG_E_INVALID, "bad mode");
+    const int tmode = is_fused_mode(mode) || mode == TCNG_MODE_AUTO ? TCNG_MODE_TILED : mode;
     mode = pauli_mode(mode, h, h->n, s->dtype);
     const WsLayout L = layout(nullptr, h, s->n_qubits, s->dtype, s->batch, mode);
     if (!ws || ws_bytes < L.total) return fail(TCNG_E_WORKSPACE, "workspace too small: need " + std::to_string(L.total));
     hipStream_t st = static_cast<hipStream_t>(stream);
+    if (use_small(tmode, h->n, s->dtype))
+        return run_small(small_job(nullptr, nullptr, h, s, nullptr, out), s, F_PAULI_TILE, st);
     double* epart = reinterpret_cast<double*>(static_cast<char*>(ws) + L.epart_off);
     const Job J = make_job(nullptr, h, s, nullptr, nullptr, nullptr, epart, L);
     tcng_status e = s->dtype == TCNG_C64 ? run_pauli<float, PAULI_RB>(h, s, nullptr, L, epart, mode, J, st)
@@ -1027,10 +1108,13 @@ tcng_status tcng_apply_pauli(const tcng_state* psi, const tcng_pauli_sum* h, con
         return fail(TCNG_E_INVALID, "output state must match the input's qubits, dtype, batch and stride");
     if (out->amps == psi->amps) return fail(TCNG_E_INVALID, "the output must not alias the input state");
     if (!valid_mode(mode)) return fail(TCNG_E_INVALID, "bad mode");
+    const int tmode = is_fused_mode(mode) || mode == TCNG_MODE_AUTO ? TCNG_MODE_TILED : mode;
     mode = pauli_mode(mode, h, h->n, psi->dtype);
     const WsLayout L = layout(nullptr, h, psi->n_qubits, psi->dtype, psi->batch, mode);
     if (!ws || ws_bytes < L.total) return fail(TCNG_E_WORKSPACE, "workspace too small: need " + std::to_string(L.total));
     hipStream_t st = static_cast<hipStream_t>(stream);
+    if (use_small(tmode, h->n, psi->dtype))
+        return run_small(small_job(nullptr, nullptr, h, psi, out->amps, energy), psi, F_PAULI_TILE, st);
     double* epart = reinterpret_cast<double*>(static_cast<char*>(ws) + L.epart_off);
     const Job J = make_job(nullptr, h, psi, out->amps, nullptr, nullptr, epart, L);
     tcng_status e = psi->dtype == TCNG_C64 ? run_pauli<float, PAULI_RB>(h, psi, out->amps, L, epart, mode, J, st)
@@ -1105,6 +1189,20 @@ tcng_status tcng_expect_grad(const tcng_circuit* c, const void* params, const tc
                                          gate_grad, S.gate_slot, c->u2m[dt], c->gate_mat, int(c->gates.size()), red,
                                          st));
         return ok();
+    }
+    if (use_small(mode, psi->n_qubits, dt)) {
+        SmallJob S = small_job(c, params, h, psi, lam->amps, energy);
+        S.slots = red;   // (the row sums' place: a value per slot and member)
+        S.total_slots = c->plain.total;
+        S.slot_ptr = c->plain.ptr;
+        S.slot_idx = c->plain.idx;
+        S.gate_slot = c->plain.gate_slot;
+        S.u2m = c->u2m[dt];
+        S.gate_mat = c->gate_mat;
+        S.grad = c->n_params ? grad : nullptr;
+        S.gate_grad = gate_grad;
+        S.do_rev = 1;
+        return run_small(S, psi, F_REV_TILE, st);
     }
     const bool ctiled = use_tiled(mode, psi->n_qubits, dt);
     void* opm = ctiled ? w + L.opm_off : nullptr;

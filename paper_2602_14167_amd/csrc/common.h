@@ -249,6 +249,22 @@ struct PPass {
     int32_t local_qubit[16];
 };
 
+// Small states (kern_small.hip): the gates in circuit order; chunks of them
+// share the workgroup's LDS tables.
+constexpr int SM_QUBITS = 10;    // largest state of one workgroup
+constexpr int SM_OPS = 192;      // gates of a chunk
+constexpr int SM_MAT = 1024;     // matrix entries of a chunk (4 or 16 per gate)
+constexpr int SM_TERMS = 256;    // Pauli groups, classes and terms kept in LDS (each)
+struct SOp {
+    int32_t kind, q0, q1;   // q1 = -1: one qubit
+    int32_t slot;           // first gradient slot (gate order), -1 none
+    int32_t p0, p1, mat;
+    int32_t mpos;           // place of its matrix in the chunk's table
+};
+struct SChunk {
+    int32_t op_begin, op_end;
+};
+
 // Pauli sum grouped by X-mask over the full index space (plain path).
 struct PTermFull {
     uint64_t z;

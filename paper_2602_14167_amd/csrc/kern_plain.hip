@@ -9,7 +9,9 @@
 // itself one 16-byte vector.  Two-qubit gates work on quads the same way.
 // Gate matrices are rebuilt per batch member from the device angles, so one
 // launch serves every parameter set of a batch (blockIdx.y = member).
+#include "finish.h"
 #include "gates.h"
+#include "plaingate.h"
 #include "kernels.h"
 
 #include <algorithm>
@@ -41,58 +43,6 @@ __device__ __forceinline__ double block_sum(double v, double* sh) {
     if (threadIdx.x == 0)
         for (int w = 0; w < NTHREADS / 64; ++w) s += sh[w];
     return s;
-}
-
-// build the (possibly inverted) 2x2 / 4x4 matrix of a gate for batch member b
-template <typename R>
-__device__ __forceinline__ void gate_mat1(int kind, const R* prm, int p0, const cx<R>* cm, int mat,
-                                          const cx<R>* umat, bool inv, cx<R> u[4]) {
-    if (umat) {
-        u[0] = umat[0]; u[1] = umat[1]; u[2] = umat[2]; u[3] = umat[3];
-    } else if (kind_diagonal(kind)) {
-        cx<R> d[2];
-        diag1<R>(kind, prm, p0, d);
-        u[0] = d[0]; u[1] = {R(0), R(0)}; u[2] = {R(0), R(0)}; u[3] = d[1];
-    } else {
-        mat1<R>(kind, prm, p0, cm, mat, u);
-    }
-    if (inv) dagger_inplace<R, 2>(u);
-}
-
-template <typename R>
-__device__ __forceinline__ void gate_mat2(int kind, const R* prm, int p0, int p1, const cx<R>* cm, int mat,
-                                          const cx<R>* umat, bool inv, cx<R> u[16]) {
-    if (umat) {
-#pragma unroll
-        for (int i = 0; i < 16; ++i) u[i] = umat[i];
-    } else if (kind == K_FSIM || kind == K_U2) {
-        mat2<R>(kind, prm, p0, p1, cm, mat, u);
-    } else {
-#pragma unroll
-        for (int i = 0; i < 16; ++i) u[i] = {R(0), R(0)};
-        if (kind == K_CNOT) {
-            u[0] = {R(1), R(0)}; u[5] = {R(1), R(0)}; u[11] = {R(1), R(0)}; u[14] = {R(1), R(0)};
-        } else {
-            cx<R> d[4];
-            diag2<R>(kind, prm, p0, d);
-            u[0] = d[0]; u[5] = d[1]; u[10] = d[2]; u[15] = d[3];
-        }
-    }
-    if (inv) dagger_inplace<R, 4>(u);
-}
-
-template <typename R>
-__device__ __forceinline__ void mv2(const cx<R>* u, cx<R>& a0, cx<R>& a1) {
-    const cx<R> x0 = a0, x1 = a1;
-    a0 = cfma(u[1], x1, u[0] * x0);
-    a1 = cfma(u[3], x1, u[2] * x0);
-}
-
-template <typename R>
-__device__ __forceinline__ void mv4(const cx<R>* u, cx<R>* x) {
-    const cx<R> x0 = x[0], x1 = x[1], x2 = x[2], x3 = x[3];
-#pragma unroll
-    for (int a = 0; a < 4; ++a) x[a] = cfma(u[4 * a + 3], x3, cfma(u[4 * a + 2], x2, cfma(u[4 * a + 1], x1, u[4 * a] * x0)));
 }
 
 // 16-byte streaming access: two complex64 or one complex128 amplitude per
@@ -426,65 +376,6 @@ __global__ void __launch_bounds__(256) k_rowsum(const RowTable a, const RowTable
     for (; i < len; i += 64) v += p[i];
     v = wave_sum(v);
     if (lane == 0) (second ? b.out : a.out)[row] = v;
-}
-
-// final sums: one thread per (member, output), fixed order everywhere
-// output k of one circuit: k = 0 energy, 1..n_params gradient, then 16 per gate
-// (when gate_grad is wanted): its 15 Lie-algebra derivatives and one idle
-// (one thread per gate left most of a wave's work to 15 serial traces: 171 us
-// for 60 circuits of 12 to 20 qubits)
-__device__ void finish_one(const FinishJob& F, int64_t k) {
-    const double* sl = F.slots;
-    if (k == 0) {
-        double e = 0.0;
-        for (int i = 0; i < F.erows; ++i) e += F.erow[i];
-        F.energy[0] = e;
-    } else if (k <= F.n_params) {
-        const int p = int(k - 1);
-        double g = 0.0;
-        for (int i = F.slot_ptr[p]; i < F.slot_ptr[p + 1]; ++i) g += sl[F.slot_idx[i]];
-        F.grad[p] = g;
-    } else {
-        // per U2 gate: dE/dalpha_k = Im tr(G^dag P_k U), P_k = sigma_a (x) sigma_b, k = 4a + b - 1
-        const int64_t r = k - 1 - F.n_params;
-        const int gi = int(r / GATE_OUTS), kk = int(r % GATE_OUTS);
-        if (kk == 15) return;
-        double* out = F.gate_grad + size_t(gi) * 15;
-        const int s0 = F.gate_slot[gi];
-        if (s0 < 0) {
-            out[kk] = 0.0;
-            return;
-        }
-        const double* U = F.u2m + size_t(F.gate_mat[gi]) * 32;
-        // single-qubit Paulis: entry (r, c) of sigma_a as (re, im)
-        auto sig = [](int a, int r, int c, double& re, double& im) {
-            re = 0.0; im = 0.0;
-            if (a == 0) re = (r == c) ? 1.0 : 0.0;
-            else if (a == 1) re = (r != c) ? 1.0 : 0.0;
-            else if (a == 2) im = (r == c) ? 0.0 : (r == 0 ? -1.0 : 1.0);
-            else re = (r == c) ? (r == 0 ? 1.0 : -1.0) : 0.0;
-        };
-        const int a = (kk + 1) >> 2, c = (kk + 1) & 3;
-        double tr_im = 0.0;
-        for (int x = 0; x < 4; ++x)
-            for (int y = 0; y < 4; ++y) {
-                // (P U)[y][x] = sum_z P[y][z] U[z][x]
-                double pur = 0.0, pui = 0.0;
-                for (int z = 0; z < 4; ++z) {
-                    double s1r, s1i, s2r, s2i;
-                    sig(a, y >> 1, z >> 1, s1r, s1i);
-                    sig(c, y & 1, z & 1, s2r, s2i);
-                    const double pr = s1r * s2r - s1i * s2i, pi = s1r * s2i + s1i * s2r;
-                    const double ur = U[2 * (4 * z + x)], ui = U[2 * (4 * z + x) + 1];
-                    pur += pr * ur - pi * ui;
-                    pui += pr * ui + pi * ur;
-                }
-                // conj(G[y][x]) * (PU)[y][x]
-                const double gr = sl[s0 + 2 * (4 * y + x)], gim = sl[s0 + 2 * (4 * y + x) + 1];
-                tr_im += gr * pui - gim * pur;
-            }
-        out[kk] = tr_im;
-    }
 }
 
 __global__ void k_finish(const double* __restrict__ slots, int total_slots, const int32_t* __restrict__ slot_ptr,

@@ -1,0 +1,382 @@
+// Whole evaluations of small states, one workgroup per batch member: forward
+// sweep, H psi and <H>, adjoint sweep, gate derivatives and final sums in one
+// launch, with the state and the costate in LDS.
+//
+// What bounds a call on so small a state is latency.  On the per-gate kernels
+// it is one launch per gate and sweep: 140 launches and 0.6 ms for 69 gates on
+// 8 qubits and 32 parameter sets.  Here a gate costs one LDS round trip and one
+// barrier (none while one wave holds all pairs), its matrix comes from an LDS
+// table that the workgroup forms at the start, one thread per gate, and a
+// derivative is one sum over the wave, added over the waves at the end.  The
+// gates are applied one by one in circuit order with the per-gate kernels'
+// matrices (plaingate.h), products and roundings, so complex64 amplitudes agree
+// with theirs to the last bit; only the float64 sums are taken in another order.
+// Measured, 8 qubits, 69 gates, 32 parameter sets, complex64: 0.64 ms a call
+// before, 0.106 ms now, of which the kernel is 77 us.  (Runs of gates multiplied
+// into 4 x 4 matrices first took 50 us, but round differently: energies and
+// gradients moved by 1e-6.)
+#include "devutil.h"
+#include "finish.h"
+#include "plaingate.h"
+
+namespace tcng {
+
+namespace {
+
+constexpr int SM_THREADS = 256;
+
+// LDS layout of a workgroup (bytes): the host sizes the launch with it, by the
+// circuit's own tables, so small circuits share a compute unit
+template <typename R>
+struct SmallLds {
+    size_t psi, lam, mat, ops, red, cot, groups, classes, terms, total;
+    __host__ __device__ SmallLds(const SmallJob& J, int nwaves) {
+        const size_t st = (size_t(1) << J.n) * sizeof(cx<R>);
+        psi = 0;
+        lam = psi + st;
+        mat = lam + st;
+        ops = mat + size_t(J.tab_mat) * sizeof(cx<R>);
+        red = ops + size_t(J.tab_ops) * sizeof(SOp);
+        cot = red + size_t(J.tab_ops) * 2 * nwaves * sizeof(double);
+        groups = cot + (J.gate_grad ? size_t(2) * 32 * nwaves * sizeof(double) : 0);
+        classes = groups + size_t(J.tab_groups) * sizeof(PGroupFull);
+        terms = classes + size_t(J.tab_classes) * sizeof(PClassFull);
+        total = terms + size_t(J.tab_terms) * sizeof(PTermFull) + SM_THREADS / 64 * sizeof(double);
+    }
+};
+
+__device__ __forceinline__ uint32_t insert_zero(uint32_t v, int q) { return ((v >> q) << (q + 1)) | (v & ((1u << q) - 1u)); }
+
+// order of the LDS operations between gates: a barrier, or nothing but program
+// order while one wave does all of them
+__device__ __forceinline__ void gate_sync(bool many) {
+    if (many) __syncthreads();
+    else {
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    }
+}
+
+// u x with the roundings written out: of the products of a sum, the one that is
+// rounded first (the compiler's own choice varies between copies of the
+// expression u x).  The imaginary part rounds u.im x.re first, or (SWAP) u.re x.im.
+template <bool SWAP, typename R>
+__device__ __forceinline__ cx<R> rmul(cx<R> u, cx<R> x) {
+    return {fmaR(u.re, x.re, -(u.im * x.im)),
+            SWAP ? fmaR(u.im, x.re, u.re * x.im) : fmaR(u.re, x.im, u.im * x.re)};
+}
+template <typename R>
+__device__ __forceinline__ void pair_mul(const cx<R>* u, cx<R>& a0, cx<R>& a1) {
+    const cx<R> x0 = a0, x1 = a1;
+    a0 = cfma(u[1], x1, rmul<false>(u[0], x0));
+    a1 = cfma(u[3], x1, rmul<false>(u[2], x0));
+}
+template <bool SWAP, typename R>
+__device__ __forceinline__ void quad_mul(const cx<R>* u, cx<R>* x) {
+    const cx<R> x0 = x[0], x1 = x[1], x2 = x[2], x3 = x[3];
+#pragma unroll
+    for (int a = 0; a < 4; ++a)
+        x[a] = cfma(u[4 * a + 3], x3, cfma(u[4 * a + 2], x2, cfma(u[4 * a + 1], x1, rmul<SWAP>(u[4 * a], x0))));
+}
+
+template <typename R>
+__device__ __forceinline__ cx<R> dag(const cx<R>* u, int dim, int a, int b, bool inv) {
+    return inv ? conj(u[b * dim + a]) : u[a * dim + b];
+}
+
+// a two-qubit gate (or its inverse) on one quad; x: local index, q0 = most
+// significant; swap: the per-gate forward kernel's copy for single quads
+template <typename R>
+__device__ __forceinline__ void quad_apply(int kind, const cx<R>* u, bool inv, bool swap, cx<R>* x) {
+    if (kind == K_CNOT) {   // (exact either way: the dense product adds zeros)
+        const cx<R> s = x[2];
+        x[2] = x[3];
+        x[3] = s;
+    } else {
+        cx<R> m[16];
+#pragma unroll
+        for (int a = 0; a < 4; ++a)
+#pragma unroll
+            for (int b = 0; b < 4; ++b) m[4 * a + b] = dag(u, 4, a, b, inv);
+        if (swap) quad_mul<true>(m, x);
+        else quad_mul<false>(m, x);
+    }
+}
+
+template <typename R>
+__global__ void __launch_bounds__(SM_THREADS) k_small(const SmallJob J) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int n = J.n, T = blockDim.x, t = threadIdx.x;
+    const int nwaves = T >> 6;
+    const int wave = uniform(t >> 6), lane = t & 63;
+    const uint32_t dim = 1u << n, pairs = dim >> 1, quads = dim >> 2;
+    const bool many = T > 64;
+    const SmallLds<R> L(J, nwaves);
+    cx<R>* psi = reinterpret_cast<cx<R>*>(smem + L.psi);
+    cx<R>* lam = reinterpret_cast<cx<R>*>(smem + L.lam);
+    cx<R>* mat = reinterpret_cast<cx<R>*>(smem + L.mat);
+    SOp* ops = reinterpret_cast<SOp*>(smem + L.ops);
+    double* red = reinterpret_cast<double*>(smem + L.red);
+    double* cot = reinterpret_cast<double*>(smem + L.cot);
+    double* esum = reinterpret_cast<double*>(smem + L.total) - SM_THREADS / 64;
+    const int64_t b = blockIdx.x;
+    cx<R>* gpsi = static_cast<cx<R>*>(J.psi) + b * J.stride;
+    cx<R>* glam = J.lam ? static_cast<cx<R>*>(J.lam) + b * J.stride : nullptr;
+    const R* prm = J.params ? static_cast<const R*>(J.params) + b * J.n_params : nullptr;
+    const cx<R>* cm = static_cast<const cx<R>*>(J.cm);
+    double* slots = J.slots ? J.slots + b * J.total_slots : nullptr;
+
+    for (uint32_t i = t; i < dim; i += T) psi[i] = gpsi[i];
+    // the Pauli sum's tables, where they fit the launch's LDS
+    const PGroupFull* groups = J.groups;
+    const PClassFull* classes = J.classes;
+    const PTermFull* terms = J.terms;
+    if (J.tab_groups) {
+        PGroupFull* lg = reinterpret_cast<PGroupFull*>(smem + L.groups);
+        PClassFull* lc = reinterpret_cast<PClassFull*>(smem + L.classes);
+        PTermFull* lt = reinterpret_cast<PTermFull*>(smem + L.terms);
+        for (int i = t; i < J.tab_groups; i += T) lg[i] = groups[i];
+        for (int i = t; i < J.tab_classes; i += T) lc[i] = classes[i];
+        for (int i = t; i < J.tab_terms; i += T) lt[i] = terms[i];
+        groups = lg;
+        classes = lc;
+        terms = lt;
+    }
+
+    // gates [begin, end) of chunk k and their matrices
+    auto chunk = [&](int k) { return k ? J.chunks[k] : J.chunk0; };
+    auto build = [&](const SChunk& C) {
+        for (int i = t; i < C.op_end - C.op_begin; i += T) {
+            const SOp o = J.ops[C.op_begin + i];
+            ops[i] = o;
+            if (o.q1 >= 0) gate_mat2<R>(o.kind, prm, o.p0, o.p1, cm, o.mat, nullptr, false, mat + o.mpos);
+            else gate_mat1<R>(o.kind, prm, o.p0, cm, o.mat, nullptr, false, mat + o.mpos);
+        }
+        __syncthreads();
+    };
+
+    if (J.do_fwd)
+        for (int k = 0; k < J.n_chunks; ++k) {
+            const SChunk C = chunk(k);
+            if (k) __syncthreads();   // the previous chunk's tables
+            build(C);
+            const int nops = C.op_end - C.op_begin;
+            SOp next = ops[0];
+            for (int i = 0; i < nops; ++i) {
+                const int kind = uniform(next.kind), q0 = uniform(next.q0), q1 = uniform(next.q1);
+                const cx<R>* u = mat + uniform(next.mpos);
+                next = ops[i + 1 < nops ? i + 1 : i];
+                if (q1 < 0) {
+                    const cx<R> m[4] = {u[0], u[1], u[2], u[3]};
+                    const uint32_t b0 = 1u << q0;
+                    for (uint32_t w = t; w < pairs; w += T) {
+                        const uint32_t i0 = insert_zero(w, q0);
+                        cx<R> x0 = psi[i0], x1 = psi[i0 | b0];
+                        pair_mul(m, x0, x1);
+                        psi[i0] = x0;
+                        psi[i0 | b0] = x1;
+                    }
+                } else {
+                    const uint32_t b0 = 1u << q0, b1 = 1u << q1;
+                    const int lo = q0 < q1 ? q0 : q1, hi = q0 < q1 ? q1 : q0;
+                    for (uint32_t w = t; w < quads; w += T) {
+                        const uint32_t i0 = insert_zero(insert_zero(w, lo), hi);
+                        cx<R> x[4] = {psi[i0], psi[i0 | b1], psi[i0 | b0], psi[i0 | b0 | b1]};
+                        quad_apply<R>(kind, u, false, lo == 0 || n == 2, x);
+                        psi[i0] = x[0];
+                        psi[i0 | b1] = x[1];
+                        psi[i0 | b0] = x[2];
+                        psi[i0 | b0 | b1] = x[3];
+                    }
+                }
+                gate_sync(many);
+            }
+        }
+    __syncthreads();
+
+    if (J.do_pauli) {
+        double e = 0.0;
+        for (uint32_t i = t; i < dim; i += T) {
+            const cx<R> pj = psi[i];
+            cx<R> acc = {R(0), R(0)};
+            for (int g = 0; g < J.n_groups; ++g) {
+                const PGroupFull G = groups[g];
+                const uint32_t j = i ^ uint32_t(G.x);
+                const cx<R> pp = psi[j];
+                double cre = 0.0, cim = 0.0;
+                for (int c = G.class_begin; c < G.class_end; ++c) {
+                    const PClassFull K = classes[c];
+                    int odd = 0;
+                    for (int m = K.term_begin; m < K.term_end; ++m) odd += __popc(j & uint32_t(terms[m].z)) & 1;
+                    const double s = double(K.term_end - K.term_begin - 2 * odd);
+                    cre = fma(K.cre, s, cre);
+                    cim = fma(K.cim, s, cim);
+                }
+                acc = cfma(cx<R>{R(cre), R(cim)}, pp, acc);
+                const double rr = fma(double(pj.re), double(pp.re), double(pj.im) * double(pp.im));
+                const double ri = fma(double(pj.re), double(pp.im), -double(pj.im) * double(pp.re));
+                e += cre * rr - cim * ri;
+            }
+            if (J.do_rev) lam[i] = acc;
+            else if (glam) glam[i] = acc;
+        }
+        e = wave_sum(e);
+        if (lane == 0) esum[wave] = e;
+        __syncthreads();
+        if (t == 0 && J.energy) {
+            double s = 0.0;
+            for (int w = 0; w < nwaves; ++w) s += esum[w];
+            J.energy[b] = s;
+        }
+    }
+
+    if (J.do_rev) {
+        for (int k = J.n_chunks - 1; k >= 0; --k) {
+            const SChunk C = chunk(k);
+            if (J.n_chunks > 1) build(C);   // (one chunk: the forward sweep's tables stand)
+            const int nops = C.op_end - C.op_begin;
+            int buf = 0;
+            SOp next = ops[nops - 1];
+            for (int i = nops - 1; i >= 0; --i) {
+                const int kind = uniform(next.kind), q0 = uniform(next.q0), q1 = uniform(next.q1);
+                const int slot = uniform(next.slot);
+                const cx<R>* u = mat + uniform(next.mpos);
+                next = ops[i > 0 ? i - 1 : 0];
+                double g0 = 0.0, g1 = 0.0;
+                if (q1 < 0) {
+                    const cx<R> m[4] = {conj(u[0]), conj(u[2]), conj(u[1]), conj(u[3])};
+                    const uint32_t b0 = 1u << q0;
+                    for (uint32_t w = t; w < pairs; w += T) {
+                        const uint32_t i0 = insert_zero(w, q0);
+                        cx<R> x0 = psi[i0], x1 = psi[i0 | b0], l0 = lam[i0], l1 = lam[i0 | b0];
+                        if (slot >= 0) {
+                            if (kind == K_RX) g0 += im_conj_mul(l0, x1) + im_conj_mul(l1, x0);
+                            else if (kind == K_RY) g0 += re_conj_mul(l1, x0) - re_conj_mul(l0, x1);
+                            else g0 += im_conj_mul(l0, x0) - im_conj_mul(l1, x1);   // RZ
+                        }
+                        pair_mul(m, x0, x1);
+                        pair_mul(m, l0, l1);
+                        psi[i0] = x0;
+                        psi[i0 | b0] = x1;
+                        lam[i0] = l0;
+                        lam[i0 | b0] = l1;
+                    }
+                } else {
+                    const uint32_t b0 = 1u << q0, b1 = 1u << q1;
+                    const int lo = q0 < q1 ? q0 : q1, hi = q0 < q1 ? q1 : q0;
+                    const bool want_cot = kind == K_U2 && slot >= 0 && J.gate_grad;
+                    double G[32];
+                    if (want_cot)
+#pragma unroll
+                        for (int e = 0; e < 32; ++e) G[e] = 0.0;
+                    for (uint32_t w = t; w < quads; w += T) {
+                        const uint32_t i0 = insert_zero(insert_zero(w, lo), hi);
+                        const uint32_t ix[4] = {i0, i0 | b1, i0 | b0, i0 | b0 | b1};
+                        cx<R> x[4], l[4];
+#pragma unroll
+                        for (int a = 0; a < 4; ++a) {
+                            x[a] = psi[ix[a]];
+                            l[a] = lam[ix[a]];
+                        }
+                        if (kind == K_RZZ) {
+                            g0 += im_conj_mul(l[0], x[0]) - im_conj_mul(l[1], x[1]) - im_conj_mul(l[2], x[2]) +
+                                  im_conj_mul(l[3], x[3]);
+                        } else if (kind == K_FSIM) {
+                            g0 += 2.0 * (im_conj_mul(l[1], x[2]) + im_conj_mul(l[2], x[1]));
+                            g1 += 2.0 * im_conj_mul(l[3], x[3]);
+                        }
+                        quad_apply<R>(kind, u, true, false, x);
+                        if (want_cot)
+#pragma unroll
+                            for (int a = 0; a < 4; ++a)
+#pragma unroll
+                                for (int c = 0; c < 4; ++c) {
+                                    G[2 * (4 * a + c)] += fma(double(l[a].re), double(x[c].re), double(l[a].im) * double(x[c].im));
+                                    G[2 * (4 * a + c) + 1] += fma(double(l[a].im), double(x[c].re), -double(l[a].re) * double(x[c].im));
+                                }
+                        quad_apply<R>(kind, u, true, false, l);
+#pragma unroll
+                        for (int a = 0; a < 4; ++a) {
+                            psi[ix[a]] = x[a];
+                            lam[ix[a]] = l[a];
+                        }
+                    }
+                    if (want_cot) {   // (two buffers: the last barrier orders the one before last)
+                        double* dst = cot + buf * 32 * nwaves;
+#pragma unroll
+                        for (int e = 0; e < 32; ++e) {
+                            const double s = wave_sum(G[e]);
+                            if (lane == 0) dst[e * nwaves + wave] = s;
+                        }
+                        gate_sync(many);
+                        if (t < 32) {
+                            double s = 0.0;
+                            for (int w = 0; w < nwaves; ++w) s += dst[t * nwaves + w];
+                            slots[slot + t] = s;
+                        }
+                        buf ^= 1;
+                        continue;
+                    }
+                }
+                if (slot >= 0 && kind != K_U2) {
+                    g0 = wave_sum(g0);
+                    if (kind == K_FSIM) g1 = wave_sum(g1);
+                    if (lane == 0) {
+                        red[(2 * i) * nwaves + wave] = g0;
+                        red[(2 * i + 1) * nwaves + wave] = g1;
+                    }
+                }
+                gate_sync(many);
+            }
+            __syncthreads();
+            for (int i = t; i < nops; i += T) {
+                const SOp o = ops[i];
+                if (o.slot < 0 || o.kind == K_U2) continue;
+                for (int p = 0; p < (o.kind == K_FSIM ? 2 : 1); ++p) {
+                    double s = 0.0;
+                    for (int w = 0; w < nwaves; ++w) s += red[(2 * i + p) * nwaves + w];
+                    slots[o.slot + p] = s;
+                }
+            }
+            __syncthreads();
+        }
+    }
+
+    if (J.do_fwd)
+        for (uint32_t i = t; i < dim; i += T) gpsi[i] = psi[i];
+    if (J.do_rev) {
+        for (uint32_t i = t; i < dim; i += T) glam[i] = lam[i];
+        FinishJob F{};
+        F.slots = slots;
+        F.slot_ptr = J.slot_ptr;
+        F.slot_idx = J.slot_idx;
+        F.gate_slot = J.gate_slot;
+        F.u2m = J.u2m;
+        F.gate_mat = J.gate_mat;
+        F.grad = J.grad ? J.grad + b * J.n_params : nullptr;
+        F.gate_grad = J.gate_grad ? J.gate_grad + b * J.n_gates * 15 : nullptr;
+        F.n_params = J.n_params;
+        F.n_gates = J.n_gates;
+        const int64_t per = 1 + int64_t(J.n_params) + (J.gate_grad ? GATE_OUTS * int64_t(J.n_gates) : 0);
+        for (int64_t k = 1 + t; k < per; k += T) finish_one(F, k);   // (output 0, the energy, is written)
+    }
+}
+
+}  // namespace
+
+// a thread per pair of amplitudes, up to 256
+template <typename R>
+hipError_t launch_small(const SmallJob& job, int64_t batch, hipStream_t st) {
+    if (batch <= 0) return hipSuccess;
+    if (job.n < 2 || job.n > SM_QUBITS || job.tab_ops > SM_OPS || job.tab_mat > SM_MAT) return hipErrorInvalidValue;
+    SmallJob J = job;
+    if (J.tab_groups > SM_TERMS || J.tab_classes > SM_TERMS || J.tab_terms > SM_TERMS)
+        J.tab_groups = J.tab_classes = J.tab_terms = 0;   // read in place
+    const int nt = std::max(64, std::min(SM_THREADS, 1 << (J.n - 1)));
+    hipLaunchKernelGGL((k_small<R>), dim3(unsigned(batch)), dim3(unsigned(nt)), SmallLds<R>(J, nt / 64).total, st, J);
+    return hipGetLastError();
+}
+template hipError_t launch_small<float>(const SmallJob&, int64_t, hipStream_t);
+template hipError_t launch_small<double>(const SmallJob&, int64_t, hipStream_t);
+
+}  // namespace tcng

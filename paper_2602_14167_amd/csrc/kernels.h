@@ -257,4 +257,36 @@ hipError_t launch_finish(const double* part, int total_slots, int wgs, const int
                          const double* u2_mats_c128, const int32_t* gate_mat, int n_gates, double* scratch,
                          hipStream_t st);
 
+// ---------------------------------------------------------------------------
+// small states: whole evaluations, one workgroup per member (kern_small.hip)
+// ---------------------------------------------------------------------------
+struct SmallJob {
+    const SChunk* chunks;
+    SChunk chunk0;             // the first of them (saves its load)
+    const SOp* ops;
+    const void* params;        // [batch][n_params]
+    const void* cm;            // constant matrices
+    void* psi;
+    void* lam;                 // H psi / costates; may be null without the adjoint sweep
+    double* energy;            // [batch] or null
+    const PGroupFull* groups;  // Pauli sum (the per-gate path's grouping)
+    const PClassFull* classes;
+    const PTermFull* terms;
+    double* slots;             // [batch][total_slots] scratch of the adjoint sweep
+    const int32_t* slot_ptr;   // as FinishJob
+    const int32_t* slot_idx;
+    const int32_t* gate_slot;
+    const double* u2m;
+    const int32_t* gate_mat;
+    double* grad;              // [batch][n_params] or null
+    double* gate_grad;         // [batch][n_gates][15] or null
+    int64_t stride;
+    int32_t n, n_chunks, n_params, n_gates, total_slots, n_groups;
+    int32_t tab_ops, tab_mat;                          // LDS tables: the most of any chunk,
+    int32_t tab_groups, tab_classes, tab_terms;        // and the Pauli sum's (0: read in place)
+    int32_t do_fwd, do_pauli, do_rev;
+};
+template <typename R>
+hipError_t launch_small(const SmallJob& job, int64_t batch, hipStream_t st);
+
 }  // namespace tcng

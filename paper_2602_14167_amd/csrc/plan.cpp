@@ -1067,4 +1067,34 @@ void group_pauli_full(const std::vector<PauliTermHost>& terms, std::vector<PGrou
     }
 }
 
+void plan_small(const std::vector<tcng_gate>& gates, const std::vector<int>& gate_slot, SmallPlan& out) {
+    SChunk C{0, 0};
+    int entries = 0;
+    for (size_t i = 0; i < gates.size(); ++i) {
+        const tcng_gate& g = gates[i];
+        const bool two = kind_arity(g.kind) == 2;
+        const int e = two ? 16 : 4;
+        if (C.op_end - C.op_begin == SM_OPS || entries + e > SM_MAT) {
+            out.chunks.push_back(C);
+            C.op_begin = C.op_end;
+            entries = 0;
+        }
+        SOp o{};
+        o.kind = g.kind;
+        o.q0 = g.q0;
+        o.q1 = two ? g.q1 : -1;
+        o.slot = gate_slot[i];
+        o.p0 = kind_nparams(g.kind) >= 1 ? g.p0 : -1;
+        o.p1 = kind_nparams(g.kind) >= 2 ? g.p1 : -1;
+        o.mat = g.mat;
+        o.mpos = entries;
+        out.ops.push_back(o);
+        entries += e;
+        ++C.op_end;
+        out.tab_ops = std::max(out.tab_ops, C.op_end - C.op_begin);
+        out.tab_mat = std::max(out.tab_mat, entries);
+    }
+    if (C.op_end > C.op_begin) out.chunks.push_back(C);
+}
+
 }  // namespace tcng

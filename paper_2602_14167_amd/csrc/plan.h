@@ -50,6 +50,13 @@ struct FusedPlan {
     std::vector<int32_t> slot_ptr, slot_idx, gate_slot;
 };
 
+// Gate tables of the small-state kernel.
+struct SmallPlan {
+    std::vector<SChunk> chunks;
+    std::vector<SOp> ops;
+    int tab_ops = 0, tab_mat = 0;   // most gates and matrix entries of a chunk
+};
+
 struct PauliPlan {
     TileConfig cfg{};
     std::vector<PPass> passes;
@@ -76,6 +83,9 @@ void lds_layout(int m, uint32_t v_read, uint32_t v_write, int32_t* img);
 // number of layouts of a fused plan that are not bank-conflict-free bijections
 int check_fused_layouts(const FusedPlan& P);
 std::string plan_pauli(int n, const std::vector<PauliTermHost>& terms, const TileConfig& cfg, PauliPlan& out);
+
+// gate_slot: first gradient slot per gate (-1 none)
+void plan_small(const std::vector<tcng_gate>& gates, const std::vector<int>& gate_slot, SmallPlan& out);
 
 // Plain path: terms grouped by full X-mask.
 void group_pauli_full(const std::vector<PauliTermHost>& terms, std::vector<PGroupFull>& groups,

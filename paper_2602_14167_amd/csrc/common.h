@@ -138,6 +138,7 @@ struct Pass {
 // A pass whose gates are neither kind runs on the generic tiled kernels.
 // ---------------------------------------------------------------------------
 constexpr int QREG = 5;
+constexpr int QTHR = 9;   // most thread bits of a phase (512 threads)
 constexpr int QK_GENERIC = 0, QK_ROT = 1, QK_FSIM = 2;   // QPass::kind
 
 struct QStep {
@@ -156,6 +157,8 @@ struct QPhase {
     int32_t rimg[QREG];           // cimg[R[i]]: the same for the register bits
     int32_t uimg[16];             // LDS slot of e_b in the layout before the phase
     int32_t ruimg[QREG];          // uimg[R[i]]
+    int32_t tu[QTHR], tc[QTHR];   // uimg, cimg of the non-register local bits, in increasing order (thread bits)
+    int32_t pad;
 };
 
 // The tiles' fixed LDS swizzle, a linear bijection of the local index that

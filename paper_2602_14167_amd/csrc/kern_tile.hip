@@ -737,44 +737,42 @@ constexpr int qb() { return B < QR ? B : 0; }
 template <typename R>
 constexpr int q_tile_bits() { return sizeof(R) == 4 ? 13 : 12; }
 
-// a phase's register map: the LDS positions of the thread's part of the local
-// index and of its registers, in the layout before the phase (plain) and
-// after it (through the phase's permutation C)
+// a phase's register map: the LDS byte offsets of the thread's part of the
+// local index and of its registers, in the layout before the phase (plain) and
+// after it (through the phase's permutation C); ES: bytes of an LDS element
 template <int QR>
 struct QMap {
     uint32_t tsw, ctsw;              // A_before(tpart), A_after(C(tpart))
     uint32_t rsw[QR], crsw[QR];      // A_before(e_R[i]), A_after(C(e_R[i])) (uniform)
 };
 
-template <int QR>
-__device__ __forceinline__ QMap<QR> qmap(cptr<QPhase> F, int t, int m) {
+template <int QR, int ES>
+__device__ __forceinline__ QMap<QR> qmap(cptr<QPhase> F, int t) {
     QMap<QR> q;
-    const uint32_t rmask = uint32_t(F->rmask);
 #pragma unroll
     for (int i = 0; i < QR; ++i) {
-        q.rsw[i] = uint32_t(F->ruimg[i]);
-        q.crsw[i] = uint32_t(F->rimg[i]);
+        q.rsw[i] = uint32_t(F->ruimg[i]) * ES;
+        q.crsw[i] = uint32_t(F->rimg[i]) * ES;
     }
-    // the thread's bits fill the non-register local bits in increasing order:
-    // unrolled over the local bits, with uniform control and lane masks, so the
-    // images' scalar loads are independent (a loop with a lane-dependent branch
-    // around each load serialised them, a scalar load's latency per bit)
+    // XOR of the images of the thread bits that are set, listed by the planner: one
+    // contiguous scalar load and five instructions per bit.  (Walking the local bits
+    // and skipping the register bits here gave a branch, a dependent scalar load and
+    // its wait per bit.)
     uint32_t tp = 0, ct = 0;
     const uint32_t tt = pin(uint32_t(t));   // (the masks are formed anew per phase, not kept live)
 #pragma unroll
-    for (int b = 0; b < MAX_TILE_BITS; ++b) {
-        if (b >= m || ((rmask >> b) & 1)) continue;
-        const int k = __popc(~rmask & ((1u << b) - 1u));   // the thread bit that fills local bit b
-        const uint32_t msk = 0u - ((tt >> k) & 1u);
-        tp ^= uint32_t(F->uimg[b]) & msk;
-        ct ^= uint32_t(F->cimg[b]) & msk;
+    for (int k = 0; k < QTHR; ++k) {
+        const uint32_t msk = uint32_t(__builtin_amdgcn_sbfe(int(tt), k, 1));
+        tp ^= uint32_t(F->tu[k]) & msk;
+        ct ^= uint32_t(F->tc[k]) & msk;
     }
-    q.tsw = tp;
-    q.ctsw = ct;
+    q.tsw = tp * ES;
+    q.ctsw = ct * ES;
     return q;
 }
 
-// LDS position of register j: through C (mapped) or not
+// LDS byte offset of register j: through C (mapped) or not.  (In bytes from the
+// start: scaled per access, an address took a shift beside its XOR.)
 template <bool MAPPED, int QR>
 __device__ __forceinline__ uint32_t qaddr(const QMap<QR>& q, int j) {
     uint32_t a = MAPPED ? q.ctsw : q.tsw;
@@ -782,6 +780,14 @@ __device__ __forceinline__ uint32_t qaddr(const QMap<QR>& q, int j) {
     for (int i = 0; i < QR; ++i)
         if ((j >> i) & 1) a ^= MAPPED ? q.crsw[i] : q.rsw[i];
     return a;
+}
+template <typename T>
+__device__ __forceinline__ T& lds_at(T* lds, uint32_t byte) {
+    return *reinterpret_cast<T*>(reinterpret_cast<char*>(lds) + byte);
+}
+template <typename T>
+__device__ __forceinline__ const T& lds_at(const T* lds, uint32_t byte) {
+    return *reinterpret_cast<const T*>(reinterpret_cast<const char*>(lds) + byte);
 }
 
 // (each call forms its addresses anew: shared between calls, the compiler
@@ -792,7 +798,7 @@ __device__ __forceinline__ QBlk<R, QR> q_read(const cx<R>* lds, QMap<QR> q) {
     q.ctsw = pin(q.ctsw);
     QBlk<R, QR> a;
 #pragma unroll
-    for (int j = 0; j < (1 << QR); ++j) a.v[j] = lds[qaddr<MAPPED>(q, j)];
+    for (int j = 0; j < (1 << QR); ++j) a.v[j] = lds_at(lds, qaddr<MAPPED>(q, j));
     return a;
 }
 template <bool MAPPED, typename R, int QR>
@@ -800,7 +806,7 @@ __device__ __forceinline__ void q_write(cx<R>* lds, const QBlk<R, QR>& a, QMap<Q
     q.tsw = pin(q.tsw);
     q.ctsw = pin(q.ctsw);
 #pragma unroll
-    for (int j = 0; j < (1 << QR); ++j) lds[qaddr<MAPPED>(q, j)] = a.v[j];
+    for (int j = 0; j < (1 << QR); ++j) lds_at(lds, qaddr<MAPPED>(q, j)) = a.v[j];
 }
 
 // Coefficients of a step, one block per (member, step) written once per
@@ -896,11 +902,11 @@ struct QTileAddr {
     static constexpr int EB = QR - (VN == 2 ? 1 : 0);
     uint64_t hb[EB];       // global offsets of the element-index bits (uniform)
     uint64_t off_t;        // the thread's part
-    uint32_t lsw_t;        // swz(VN t)
-    uint32_t lhb[EB];      // swz of the element-index bits (uniform)
+    uint32_t lsw_t;        // LDS byte offset: swz(VN t)
+    uint32_t lhb[EB];      // and swz of the element-index bits (uniform)
 };
 
-template <typename R, int QR>
+template <typename R, int QR, int ES>
 __device__ __forceinline__ QTileAddr<R, QR> q_tile_addr(const PassInfo& pi, int t) {
     using A_t = QTileAddr<R, QR>;
     A_t A;
@@ -912,10 +918,10 @@ __device__ __forceinline__ QTileAddr<R, QR> q_tile_addr(const PassInfo& pi, int 
         for (int i = 0; i < MAX_TILE_BITS; ++i)
             if (i == b0 + k) q = pi.lq[i];
         A.hb[k] = uint64_t(1) << q;
-        A.lhb[k] = swz(1u << (b0 + k));
+        A.lhb[k] = swz(1u << (b0 + k)) * ES;
     }
     A.off_t = loc2glob(uint32_t(t * A_t::VN), pi.lo, pi.m, pi.lq);
-    A.lsw_t = swz(uint32_t(t * A_t::VN));
+    A.lsw_t = swz(uint32_t(t * A_t::VN)) * ES;
     return A;
 }
 
@@ -965,7 +971,7 @@ __device__ __forceinline__ void q_tile_put(cx<R>* lds, const QTileRegs<R, QR>& r
     for (int it = 0; it < (1 << QR) / VN; ++it) {
         const uint32_t e = lt ^ q_loff<R, QR>(A, it);
 #pragma unroll
-        for (int k = 0; k < VN; ++k) lds[e ^ uint32_t(k)] = r.v[it * VN + k];
+        for (int k = 0; k < VN; ++k) lds_at(lds, e ^ uint32_t(k * sizeof(cx<R>))) = r.v[it * VN + k];
     }
 }
 
@@ -982,7 +988,7 @@ __device__ __forceinline__ void q_tile_store(const cx<R>* lds, gptr<cx<R>> psi, 
         cx<R> v[VN];
 #pragma unroll
         for (int k = 0; k < VN; ++k) {
-            v[k] = lds[e ^ uint32_t(k)];
+            v[k] = lds_at(lds, e ^ uint32_t(k * sizeof(cx<R>)));
             if (flip) v[k] = {sg * v[k].re, sg * v[k].im};
         }
         V16<R>::store(p + (base + q_goff<R, QR>(A, it)), v);
@@ -1015,6 +1021,7 @@ __device__ __forceinline__ void q_red_fs(double* red, const int32_t* slot, int n
 template <typename R, int QR, bool FS>
 __global__ void __launch_bounds__(1 << (q_tile_bits<R>() - QR)) k_rounds_fwd(const JobList jl, const Job single,
                                                                            int wgs) {
+    constexpr int ES = sizeof(cx<R>);
     __shared__ cx<R> lds[Tile<R>::ELEMS];
     int64_t local;
     const Job J = load_job(jl, single, blockIdx.x, local);
@@ -1030,7 +1037,7 @@ __global__ void __launch_bounds__(1 << (q_tile_bits<R>() - QR)) k_rounds_fwd(con
     cptr<QPhase> phases = as_const(J.qphases);
     cptr<QCoef<R>> coef = as_const(reinterpret_cast<const QCoef<R>*>(J.qcoef)) + size_t(b) * J.qsteps_all;
 
-    const QTileAddr<R, QR> A = q_tile_addr<R, QR>(pi, t);
+    const QTileAddr<R, QR> A = q_tile_addr<R, QR, ES>(pi, t);
     QTileRegs<R, QR> nx;
     if (wg < J.tiles) nx = q_tile_fetch<R, QR>(psi, tile_base(uint64_t(wg), pi.tmask, J.n), A);
     for (int64_t tile = wg; tile < J.tiles; tile += wgs) {
@@ -1042,7 +1049,7 @@ __global__ void __launch_bounds__(1 << (q_tile_bits<R>() - QR)) k_rounds_fwd(con
         bool flip = false;
         for (int f = Q.phase_begin; f < Q.phase_end; ++f) {
             cptr<QPhase> F = phases + f;
-            const QMap<QR> q = qmap<QR>(F, t, pi.m);
+            const QMap<QR> q = qmap<QR, ES>(F, t);
             QBlk<R, QR> a = q_read<false>(lds, q);
             if constexpr (FS) {
                 const uint32_t hm = uint32_t(F->hmask);
@@ -1082,6 +1089,7 @@ __global__ void __launch_bounds__(1 << (q_tile_bits<R>() - QR)) k_rounds_fwd(con
 template <typename R, int QR, bool FS>
 __global__ void __launch_bounds__(1 << (q_tile_bits<R>() - QR)) k_rounds_rev(const JobList jl, const Job single) {
     constexpr int NB = 1 << QR;
+    constexpr int ES = sizeof(cx<R>);
     __shared__ cx<R> lds[Tile<R>::ELEMS];
     __shared__ double red[RED_SLOTS * ((1 << (q_tile_bits<R>() - QR)) / 64)];
     int64_t local;
@@ -1106,12 +1114,12 @@ __global__ void __launch_bounds__(1 << (q_tile_bits<R>() - QR)) k_rounds_rev(con
 
     for (int i = t; i < nslots * nwaves; i += blockDim.x) red[i] = 0.0;
     // (the first __syncthreads below orders these writes before any accumulation)
-    const QTileAddr<R, QR> A = q_tile_addr<R, QR>(pi, t);
+    const QTileAddr<R, QR> A = q_tile_addr<R, QR, ES>(pi, t);
 
     for (int64_t tile = wg; tile < J.tiles; tile += wgs) {
         const uint64_t base = tile_base(uint64_t(tile), pi.tmask, J.n);
         int f = Q.phase_end - 1;
-        QMap<QR> q = qmap<QR>(phases + f, t, pi.m);
+        QMap<QR> q = qmap<QR, ES>(phases + f, t);
         QBlk<R, QR> ps, la;
         bool flip = false;   // psi and lambda see the same rotations: one sign for both
         {
@@ -1176,7 +1184,7 @@ __global__ void __launch_bounds__(1 << (q_tile_bits<R>() - QR)) k_rounds_rev(con
             if (f == Q.phase_begin) break;
             // hand both blocks to the previous phase: written in plain order,
             // read back through that phase's permutation
-            const QMap<QR> qn = qmap<QR>(phases + (f - 1), t, pi.m);
+            const QMap<QR> qn = qmap<QR, ES>(phases + (f - 1), t);
             __syncthreads();
             q_write<false>(lds, ps, q);
             __syncthreads();

@@ -371,6 +371,12 @@ void rounds_lds_layouts(int m, QPhase* ph, int count, int qreg) {
             F.rimg[i] = i < qreg ? F.cimg[F.R[i]] : 0;
             F.ruimg[i] = i < qreg ? F.uimg[F.R[i]] : 0;
         }
+        for (int b = 0, k2 = 0; b < m && k2 < QTHR; ++b) {
+            if ((F.rmask >> b) & 1) continue;
+            F.tu[k2] = F.uimg[b];
+            F.tc[k2] = F.cimg[b];
+            ++k2;
+        }
     }
 }
 

@@ -104,4 +104,77 @@ __device__ __forceinline__ float wave_sum(float v) {
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
 }
 
+// ---------------------------------------------------------------------------
+// wave sums of N values at once (N a power of two up to 16): lane l of the
+// result holds the sum of v[l % N] over the 64 lanes.  The additions pair lanes
+// in the order of wave_sum (1, 2, 4, 8, 16, 32 apart), so every sum is the same
+// to the last bit; while lanes still hold several values each level halves
+// them (a lane keeps one of a pair and sends the other), so N = 8 sums take
+// about 30 instructions instead of 8 butterflies.
+// ---------------------------------------------------------------------------
+template <int CTRL, int BANKS>
+__device__ __forceinline__ int dpp_get(int old, int v) {
+    return __builtin_amdgcn_update_dpp(old, v, CTRL, 0xF, BANKS, false);
+}
+// the value of lane l ^ D (D = 1, 2, 4 or 8)
+template <int D>
+__device__ __forceinline__ int xor_lane(int v) {
+    if constexpr (D == 1) return dpp_get<0xB1, 0xF>(0, v);        // quad_perm [1, 0, 3, 2]
+    else if constexpr (D == 2) return dpp_get<0x4E, 0xF>(0, v);   // quad_perm [2, 3, 0, 1]
+    else if constexpr (D == 4) return dpp_get<0x114, 0xA>(dpp_get<0x104, 0x5>(0, v), v);   // row_shl:4 | row_shr:4
+    else return dpp_get<0x128, 0xF>(0, v);                        // row_ror:8
+}
+template <int D>
+__device__ __forceinline__ float xor_lane(float v) { return __int_as_float(xor_lane<D>(__float_as_int(v))); }
+template <int D>
+__device__ __forceinline__ double xor_lane(double v) {
+    const long long b = __double_as_longlong(v);
+    const int lo = xor_lane<D>(int(b)), hi = xor_lane<D>(int(b >> 32));
+    return __longlong_as_double((long long)(unsigned)lo | ((long long)hi << 32));
+}
+// v of this lane + v of lane l ^ 16 (l ^ 32)
+template <bool ROWS32>
+__device__ __forceinline__ float add_rows(float v) {
+    const unsigned u = __float_as_uint(v);
+    const auto r = ROWS32 ? __builtin_amdgcn_permlane32_swap(u, u, false, false)
+                          : __builtin_amdgcn_permlane16_swap(u, u, false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+template <bool ROWS32>
+__device__ __forceinline__ double add_rows(double v) {
+    const unsigned long long b = (unsigned long long)__double_as_longlong(v);
+    const unsigned lo = unsigned(b), hi = unsigned(b >> 32);
+    const auto rl = ROWS32 ? __builtin_amdgcn_permlane32_swap(lo, lo, false, false)
+                           : __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+    const auto rh = ROWS32 ? __builtin_amdgcn_permlane32_swap(hi, hi, false, false)
+                           : __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+    return __longlong_as_double((long long)(((unsigned long long)rh[0] << 32) | rl[0])) +
+           __longlong_as_double((long long)(((unsigned long long)rh[1] << 32) | rl[1]));
+}
+
+template <int D, int N, typename R>
+__device__ __forceinline__ R multi_level(const R* v, int lane) {
+    if constexpr (N == 1) {   // one value a lane: plain additions
+        if constexpr (D == 16) return add_rows<true>(add_rows<false>(v[0]));
+        else {
+            const R s = v[0] + xor_lane<D>(v[0]);
+            return multi_level<2 * D, 1>(&s, lane);
+        }
+    } else {
+        R w[N / 2];
+        const bool odd = (lane & D) != 0;
+#pragma unroll
+        for (int i = 0; i < N / 2; ++i) {
+            const R keep = odd ? v[2 * i + 1] : v[2 * i], send = odd ? v[2 * i] : v[2 * i + 1];
+            w[i] = keep + xor_lane<D>(send);
+        }
+        return multi_level<2 * D, N / 2>(w, lane);
+    }
+}
+template <int N, typename R>
+__device__ __forceinline__ R multi_wave_sum(const R* v, int lane) {
+    static_assert(N == 8 || N == 16, "8 or 16 values");
+    return multi_level<1, N>(v, lane);
+}
+
 }  // namespace tcng

@@ -995,25 +995,30 @@ __device__ __forceinline__ void q_tile_store(const cx<R>* lds, gptr<cx<R>> psi, 
     }
 }
 
-// a round's derivative partials into their slots (absent gates have none)
-template <int QR, typename R>
-__device__ __forceinline__ void q_red(double* red, const int32_t* slot, int nwaves, int wave, int lane,
-                                      const R* g) {
-#pragma unroll
-    for (int i = 0; i < QR; ++i)
-        if (slot[i] >= 0) red_add(red, slot[i] * nwaves + wave, g[i], lane);
+// A step's derivative partials into their slots, all of them in one reduction:
+// lane l ends with partial l % N, its slot comes from the step's own table (one
+// load per lane; -1: absent), and each lane adds its sum, in float64, to the
+// wave's copy of the slot.  (One butterfly and one atomic per partial took 6 of
+// the reverse sweep's 55 instructions per amplitude and step.)
+template <int N, typename R>
+__device__ __forceinline__ void q_red(double* red, int slot, int nwaves, int wave, int lane, const R* g) {
+    const double s = double(multi_wave_sum<N>(g, lane));
+    if (lane < N && slot >= 0)
+        (void)__hip_atomic_fetch_add(red + (slot * nwaves + wave), s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
-
-// an fSim round's (theta, phi) partials into their slots (slot, slot + 1)
-template <int NS, typename R>
-__device__ __forceinline__ void q_red_fs(double* red, const int32_t* slot, int nwaves, int wave, int lane,
-                                         const R* gt, const R* gp) {
-#pragma unroll
-    for (int i = 0; i < NS; ++i)
-        if (slot[i] >= 0) {
-            red_add(red, slot[i] * nwaves + wave, gt[i], lane);
-            red_add(red, (slot[i] + 1) * nwaves + wave, gp[i], lane);
-        }
+// the slot of lane l's partial: rotations: the RZ of register bit l in lanes
+// 0..N/2-1, the RY in the others; fSim: (theta, phi) of pair slot l / 2
+template <int N, int QR, bool FS>
+__device__ __forceinline__ int q_slot(gptr<const QStep> S, int lane) {
+    const int l = lane & (N - 1);
+    if constexpr (FS) {
+        const int v = S->sy[l >> 1];
+        return v < 0 ? -1 : v + (l & 1);
+    } else {
+        const int k = l & (N / 2 - 1);
+        if (k >= QR) return -1;
+        return l < N / 2 ? S->sz[k] : S->sy[k];
+    }
 }
 
 // forward: `wgs` workgroups per member loop over the tiles; the next tile's
@@ -1109,6 +1114,8 @@ __global__ void __launch_bounds__(1 << (q_tile_bits<R>() - QR)) k_rounds_rev(con
     gptr<cx<R>> lam = as_global(static_cast<cx<R>*>(J.costate)) + b * J.stride;
     cptr<QPhase> phases = as_const(J.qrphases);
     cptr<QStep> steps = as_const(J.qrsteps);
+    gptr<const QStep> gsteps = as_global(J.qrsteps);
+    constexpr int NR = FS || QR <= 4 ? 8 : 16;   // partials of a step's reduction
     cptr<QCoef<R>> coef = as_const(reinterpret_cast<const QCoef<R>*>(J.qcoef)) + size_t(b) * J.qsteps_all + J.qsteps_fwd;
     const int nslots = P->n_slots;
 
@@ -1140,39 +1147,43 @@ __global__ void __launch_bounds__(1 << (q_tile_bits<R>() - QR)) k_rounds_rev(con
             const int s_begin = F->step_begin;
             for (int s = F->step_end - 1; s >= s_begin; --s) {
                 const QStep S = steps[s];
+                const int slot = q_slot<NR, QR, FS>(gsteps + s, lane);
                 if constexpr (FS) {
                     cptr<R> c = &coef[s].c[0];
                     // round B, then round A, gate by gate (the gates of a round
                     // act on disjoint pairs and commute, so each one's derivative
                     // is taken just before it is un-applied); absent gates skipped
-                    R gt[4], gp[4];
-                    if (S.ry[2] >= 0) fs_unapply<QR, 1, 2>(ps, la, c + 8, gt[2], gp[2]);
+                    R g[NR] = {R(0), R(0), R(0), R(0), R(0), R(0), R(0), R(0)};
+                    if (S.ry[2] >= 0) fs_unapply<QR, 1, 2>(ps, la, c + 8, g[4], g[5]);
                     if constexpr (QR > 4)
-                        if (S.ry[3] >= 0) fs_unapply<QR, qb<3, QR>(), qb<4, QR>()>(ps, la, c + 12, gt[3], gp[3]);
-                    q_red_fs<(QR > 4 ? 2 : 1)>(red, S.sy + 2, nwaves, wave, lane, gt + 2, gp + 2);
-                    if (S.ry[0] >= 0) fs_unapply<QR, 0, 1>(ps, la, c, gt[0], gp[0]);
+                        if (S.ry[3] >= 0) fs_unapply<QR, qb<3, QR>(), qb<4, QR>()>(ps, la, c + 12, g[6], g[7]);
+                    if (S.ry[0] >= 0) fs_unapply<QR, 0, 1>(ps, la, c, g[0], g[1]);
                     if constexpr (QR > 3)
-                        if (S.ry[1] >= 0) fs_unapply<QR, 2, qb<3, QR>()>(ps, la, c + 4, gt[1], gp[1]);
-                    q_red_fs<(QR > 3 ? 2 : 1)>(red, S.sy, nwaves, wave, lane, gt, gp);
+                        if (S.ry[1] >= 0) fs_unapply<QR, 2, qb<3, QR>()>(ps, la, c + 4, g[2], g[3]);
+                    q_red<NR>(red, slot, nwaves, wave, lane, g);
                     continue;
                 }
                 cptr<R> c = &coef[s].c[0];
-                // the round's derivatives first, then the un-apply, then their
-                // reductions (which leave the blocks alone)
-                R gz[QR], gy[QR];
+                // the round's derivatives first, then the un-apply, then the step's reduction
+                // (which leaves the blocks alone)
+                R gz[QR], g[NR];
                 grad_rz_all<R, QR>(la, ps, gz);
                 ps = app_phases<true, R, NB>(ps, c + QPH);
                 la = app_phases<true, R, NB>(la, c + QPH);
-                q_red<QR>(red, S.sz, nwaves, wave, lane, gz);
-                gy[0] = grad_rot1<R, NB, 0>(K_RY, la, ps);
-                gy[1] = grad_rot1<R, NB, 1>(K_RY, la, ps);
-                gy[2] = grad_rot1<R, NB, 2>(K_RY, la, ps);
-                if constexpr (QR > 3) gy[qb<3, QR>()] = grad_rot1<R, NB, qb<3, QR>()>(K_RY, la, ps);
-                if constexpr (QR > 4) gy[qb<4, QR>()] = grad_rot1<R, NB, qb<4, QR>()>(K_RY, la, ps);
+#pragma unroll
+                for (int k = 0; k < NR / 2; ++k) {
+                    g[k] = k < QR ? gz[k < QR ? k : 0] : R(0);
+                    g[NR / 2 + k] = R(0);
+                }
+                g[NR / 2] = grad_rot1<R, NB, 0>(K_RY, la, ps);
+                g[NR / 2 + 1] = grad_rot1<R, NB, 1>(K_RY, la, ps);
+                g[NR / 2 + 2] = grad_rot1<R, NB, 2>(K_RY, la, ps);
+                if constexpr (QR > 3) g[NR / 2 + 3] = grad_rot1<R, NB, qb<3, QR>()>(K_RY, la, ps);
+                if constexpr (QR > 4) g[NR / 2 + 4] = grad_rot1<R, NB, qb<4, QR>()>(K_RY, la, ps);
                 ps = q_ry_round<true, QR>(ps, c);
                 la = q_ry_round<true, QR>(la, c);
                 flip = flip != (c[10] < R(0));
-                q_red<QR>(red, S.sy, nwaves, wave, lane, gy);
+                q_red<NR>(red, slot, nwaves, wave, lane, g);
             }
             if constexpr (FS) {   // the phase's Hadamards (their own inverses) last
                 const uint32_t hm = uint32_t(F->hmask);

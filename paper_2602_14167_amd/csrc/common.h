@@ -189,6 +189,15 @@ constexpr int FUSED_KMAX = 5;
 constexpr int FUSED_MAX_BLOCKS = 8;    // blocks per fused pass (outer-product accumulators in LDS)
 constexpr int FUSED5_MAX_BLOCKS = 4;   // the same for 32 x 32 blocks (8 accumulated entries per thread and block)
 
+// The tile index's bits deposited into the qubits outside a tile, as runs of
+// adjacent qubits: base = sum over runs of (tile & mask) << shift.
+constexpr int MAX_RUNS = 16;
+struct TileRuns {
+    uint32_t mask[MAX_RUNS];       // bits of the tile index (0 beyond n)
+    int32_t shift[MAX_RUNS];
+    int32_t n, pad;
+};
+
 struct FPhase {
     int32_t op_begin, op_end;      // gates of the block, circuit order (Op.r0/r1 = bit of j)
     int32_t R[FUSED_KMAX];         // local bit of block bit t (t < k)
@@ -211,6 +220,8 @@ struct FPass {
     int32_t local_qubit[16];
     int32_t ld[MAX_TILE_BITS];     // layout the tile load writes
     int32_t st[MAX_TILE_BITS];     // layout the tile store reads
+    uint64_t gimg[MAX_TILE_BITS];  // global offset of each local bit (0 beyond m)
+    TileRuns runs;
 };
 
 // Pauli sum, grouped by X-mask, for the tiled H|psi> / <H> passes.  Inside a

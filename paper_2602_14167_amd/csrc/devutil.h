@@ -177,4 +177,14 @@ __device__ __forceinline__ R multi_wave_sum(const R* v, int lane) {
     return multi_level<1, N>(v, lane);
 }
 
+// base offset of a tile: its index's bits in the qubits outside it (four runs
+// without a branch, as brick walls and ladders have at most; the rest in a loop)
+__device__ __forceinline__ uint64_t runs_base(uint64_t tile, cptr<TileRuns> R) {
+    uint64_t base = 0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) base |= uint64_t(uint32_t(tile) & R->mask[k]) << R->shift[k];
+    for (int k = 4; k < R->n; ++k) base |= uint64_t(uint32_t(tile) & R->mask[k]) << R->shift[k];
+    return base;
+}
+
 }  // namespace tcng

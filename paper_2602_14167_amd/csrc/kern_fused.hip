@@ -38,35 +38,6 @@ template <int MB>
 constexpr int ct_max() { return MB >= 12 ? 2 : 1; }
 constexpr int OSTRIDE = 512;             // doubles per block outer product (16 x 16 complex)
 
-__device__ __forceinline__ uint64_t loc2glob_f(uint32_t l, int lo, int m, cptr<FPass> P) {
-    uint64_t g = l & ((1u << lo) - 1);
-#pragma unroll
-    for (int i = 0; i < MAX_TILE_BITS; ++i)
-        if (i >= lo && i < m) g |= uint64_t((l >> i) & 1) << P->local_qubit[i];
-    return g;
-}
-
-__device__ __forceinline__ uint64_t tile_base_f(uint64_t tile, uint64_t tmask, int n) {
-    uint64_t base = 0;
-    int k = 0;
-    for (int q = 0; q < n; ++q) {
-        if ((tmask >> q) & 1) continue;
-        base |= ((tile >> k) & 1) << q;
-        ++k;
-    }
-    return base;
-}
-
-// address of local index l under a layout (XOR of the images of its bits;
-// masks instead of branches: l differs per lane)
-__device__ __forceinline__ uint32_t lay_c(uint32_t l, cptr<int32_t> img, int m) {
-    uint32_t a = 0;
-#pragma unroll
-    for (int b = 0; b < MAX_TILE_BITS; ++b)
-        if (b < m) a ^= uint32_t(img[b]) & (0u - ((l >> b) & 1u));
-    return a;
-}
-
 // tile HBM <-> LDS: thread t moves 16-byte chunks c = it * nthr + t (local
 // indices 2c, 2c + 1), each amplitude to its address under `img`.  Layouts and
 // the local -> global map are linear in the bits, so the thread's part
@@ -84,20 +55,48 @@ struct TileIO {
     uint32_t a1_ld, a1_st;       // images of local bit 0
 };
 
+// (The pass lists the global offset and both layouts' addresses of every local
+// bit, zero beyond the tile, so the maps are sums under lane masks of values from
+// a few wide scalar loads.  With conditions on the bit and the tile size around
+// each, the loads came one at a time: some 150 dependent scalar loads per tile.)
 template <int IT>
 __device__ __forceinline__ TileIO<IT> tile_io(cptr<FPass> P, int t, int nthr) {
+    constexpr int IB = IT == 8 ? 3 : 2;   // iteration bits
+    static_assert(IT == 4 || IT == 8, "iterations of a tile");
     TileIO<IT> io;
-    const int m = P->m, lo = P->lo;
-    const uint32_t lt = 2u * uint32_t(t);
-    io.gt = loc2glob_f(lt, lo, m, P);
-    io.at_ld = lay_c(lt, as_const(P->ld), m);
-    io.at_st = lay_c(lt, as_const(P->st), m);
+    uint32_t glo = 0, ghi = 0, ald = 0, ast = 0;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {   // thread bit k: local bit k + 1
+        const uint32_t msk = uint32_t(__builtin_amdgcn_sbfe(t, k, 1));
+        const uint64_t g = P->gimg[k + 1];
+        glo |= uint32_t(g) & msk;
+        ghi |= uint32_t(g >> 32) & msk;
+        ald ^= uint32_t(P->ld[k + 1]) & msk;
+        ast ^= uint32_t(P->st[k + 1]) & msk;
+    }
+    io.gt = (uint64_t(ghi) << 32) | glo;
+    io.at_ld = ald;
+    io.at_st = ast;
+    const int b0 = 32 - __builtin_clz(uint32_t(nthr));   // first local bit of the iteration: log2(2 nthr)
+    uint64_t g[IB];
+    uint32_t al[IB], as[IB];
+#pragma unroll
+    for (int k = 0; k < IB; ++k) {
+        g[k] = P->gimg[b0 + k];
+        al[k] = uint32_t(P->ld[b0 + k]);
+        as[k] = uint32_t(P->st[b0 + k]);
+    }
 #pragma unroll
     for (int it = 0; it < IT; ++it) {
-        const uint32_t li = 2u * uint32_t(it * nthr);
-        io.gi[it] = loc2glob_f(li, lo, m, P);
-        io.ai_ld[it] = lay_c(li, as_const(P->ld), m);
-        io.ai_st[it] = lay_c(li, as_const(P->st), m);
+        io.gi[it] = 0;
+        io.ai_ld[it] = io.ai_st[it] = 0;
+#pragma unroll
+        for (int k = 0; k < IB; ++k)
+            if ((it >> k) & 1) {
+                io.gi[it] |= g[k];
+                io.ai_ld[it] ^= al[k];
+                io.ai_st[it] ^= as[k];
+            }
     }
     io.a1_ld = uint32_t(P->ld[0]);
     io.a1_st = uint32_t(P->st[0]);
@@ -275,13 +274,13 @@ __global__ void __launch_bounds__(FTHREADS) k_fused_fwd(const JobList jl, const 
     const int t = threadIdx.x;
     const int wave = uniform(t >> 6), lane = t & 63, h = lane >> 5;
     const bool active = wave < K.nwv;
-    const int64_t b = local / J.tiles;
-    const uint64_t tile = uint64_t(local - b * J.tiles);
+    const int64_t b = local >> (J.n - m);   // 2^(n - m) tiles per member
+    const uint64_t tile = uint64_t(local) & (uint64_t(J.tiles) - 1);
     gptr<cx<float>> psi = as_global(static_cast<cx<float>*>(J.state)) + b * J.stride;
     gptr<const float> mats =
         as_global(static_cast<const float*>(J.fmats)) + size_t(J.shared ? 0 : b) * J.n_blocks * mats_stride<KB>();
     cptr<FPhase> phases = as_const(J.fphases);
-    const uint64_t base = tile_base_f(tile, P->tile_mask, J.n);
+    const uint64_t base = runs_base(tile, &P->runs);
     float2* const bufs[1] = {lds};
     const gptr<cx<float>> sts[1] = {psi};
     // the first pass may load from another state (the tiles are stored into psi)
@@ -290,6 +289,11 @@ __global__ void __launch_bounds__(FTHREADS) k_fused_fwd(const JobList jl, const 
                                          : psi};
     const TileIO<IT> io = tile_io<IT>(P, t, K.nthr);
 
+    // block matrices one phase ahead: the first phase's is in flight with the tile,
+    // the next phase's while this phase's matrix products run
+    float wn[16];
+    if constexpr (KB == 4)
+        if (active) read_mat(mats + size_t(phases[P->phase_begin].block) * 2048, lane, wn);
     if (active) {
         if (J.init_basis1 && jl.step == 0) {
             ftile_basis<IT>(lds, base, io, uint64_t(J.init_basis1 - 1));
@@ -347,10 +351,6 @@ __global__ void __launch_bounds__(FTHREADS) k_fused_fwd(const JobList jl, const 
         if (active) ftile_store<IT, 1>(bufs, sts, base, io);
         return;
     }
-    // block matrices one phase ahead: the next phase's loads are in flight
-    // while this phase's matrix products run
-    float wn[16];
-    if (active) read_mat(mats + size_t(phases[P->phase_begin].block) * 2048, lane, wn);
     __syncthreads();
     for (int f = P->phase_begin; f < f_end; ++f) {
         cptr<FPhase> F = phases + f;
@@ -569,9 +569,9 @@ __global__ void __launch_bounds__(FTHREADS, KB == 5 ? 1 : 2) k_fused_rev(const J
     bool first = true;
     const int64_t items = J.shared ? J.tiles * J.batch : J.tiles;
     for (int64_t item = wg; item < items; item += wgs) {
-        const int64_t mb = J.shared ? item / J.tiles : 0;
+        const int64_t mb = J.shared ? item >> (J.n - m) : 0;   // 2^(n - m) tiles per member
         const uint64_t base =
-            tile_base_f(uint64_t(item - mb * J.tiles), P->tile_mask, J.n) + uint64_t(mb) * uint64_t(J.stride);
+            runs_base(uint64_t(item) & (uint64_t(J.tiles) - 1), &P->runs) + uint64_t(mb) * uint64_t(J.stride);
         __syncthreads();
         if (active) ftile_load<IT, 2>(bufs, sts, base, io);
         __syncthreads();

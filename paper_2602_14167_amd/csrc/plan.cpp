@@ -67,6 +67,23 @@ std::vector<std::pair<std::pair<double, double>, std::vector<int>>> coefficient_
     return out;
 }
 
+// runs of adjacent qubits outside tile T (at most MAX_RUNS: n <= 34 qubits, 9 or more in the tile)
+TileRuns tile_runs(uint64_t T, int n) {
+    TileRuns R{};
+    int k = 0;   // next bit of the tile index
+    for (int q = 0; q < n;) {
+        if ((T >> q) & 1) { ++q; continue; }
+        int e = q;
+        while (e < n && !((T >> e) & 1)) ++e;
+        R.mask[R.n] = ((1u << (e - q)) - 1u) << k;
+        R.shift[R.n] = q - k;
+        ++R.n;
+        k += e - q;
+        q = e;
+    }
+    return R;
+}
+
 uint64_t fill_tile(uint64_t T, int n, int m) {
     for (int q = 0; q < n && popc(T) < m; ++q) T |= uint64_t(1) << q;
     return T;
@@ -721,6 +738,8 @@ std::string plan_fused(int n, const std::vector<tcng_gate>& gates, int n_params,
         for (int q = 0; q < n; ++q)
             if ((T >> q) & 1) { qubit_to_local[q] = li; P.local_qubit[li] = q; ++li; }
         if (li != m) return "internal: tile size mismatch";
+        for (int i = 0; i < m; ++i) P.gimg[i] = uint64_t(1) << P.local_qubit[i];
+        P.runs = tile_runs(T, n);
 
         // ---- blocks: a gate joins while its qubits fit in kb local bits
         // and no earlier gate of the pass left out shares a qubit with it

@@ -67,6 +67,7 @@ constexpr int MAX_TILE_BITS = 14;
 constexpr int MAX_RB = 5;
 constexpr int RED_SLOTS = 256;   // float64 gradient accumulators per wave and reverse pass
 constexpr int MAX_THREADS = 512; // threads per tile workgroup (2^(m - rb))
+constexpr int QTHR = 9;          // thread bits of a phase (at most)
 
 enum OpType : int8_t {
     OP_DENSE1 = 0,  // 2x2 matrix, operand in register bit r0
@@ -98,6 +99,17 @@ struct Op {
 struct Phase {
     int32_t op_begin, op_end;
     int32_t R[6];    // local bit position of register bit i (i < RB)
+    int32_t tb[QTHR];   // local bits of the thread bits, in increasing order (0 beyond them)
+    int32_t pad;
+};
+
+// The tile index's bits deposited into the qubits outside a tile, as runs of
+// adjacent qubits: base = sum over runs of (tile & mask) << shift.
+constexpr int MAX_RUNS = 16;
+struct TileRuns {
+    uint32_t mask[MAX_RUNS];       // bits of the tile index (0 beyond n)
+    int32_t shift[MAX_RUNS];
+    int32_t n, pad;
 };
 
 // One HBM round trip: tiles of 2^m amplitudes over the qubits in tile_mask.
@@ -109,6 +121,7 @@ struct Pass {
     int32_t n_slots, slot_base;   // reverse sweep: gradient slots [slot_base, slot_base + n_slots)
     uint64_t tile_mask;
     int32_t local_qubit[16];
+    TileRuns runs;
 };
 
 // ---------------------------------------------------------------------------
@@ -138,7 +151,6 @@ struct Pass {
 // A pass whose gates are neither kind runs on the generic tiled kernels.
 // ---------------------------------------------------------------------------
 constexpr int QREG = 5;
-constexpr int QTHR = 9;   // most thread bits of a phase (512 threads)
 constexpr int QK_GENERIC = 0, QK_ROT = 1, QK_FSIM = 2;   // QPass::kind
 
 struct QStep {
@@ -188,15 +200,6 @@ constexpr int FUSED_K = 4;
 constexpr int FUSED_KMAX = 5;
 constexpr int FUSED_MAX_BLOCKS = 8;    // blocks per fused pass (outer-product accumulators in LDS)
 constexpr int FUSED5_MAX_BLOCKS = 4;   // the same for 32 x 32 blocks (8 accumulated entries per thread and block)
-
-// The tile index's bits deposited into the qubits outside a tile, as runs of
-// adjacent qubits: base = sum over runs of (tile & mask) << shift.
-constexpr int MAX_RUNS = 16;
-struct TileRuns {
-    uint32_t mask[MAX_RUNS];       // bits of the tile index (0 beyond n)
-    int32_t shift[MAX_RUNS];
-    int32_t n, pad;
-};
 
 struct FPhase {
     int32_t op_begin, op_end;      // gates of the block, circuit order (Op.r0/r1 = bit of j)
@@ -261,6 +264,7 @@ struct PPass {
     int32_t m, lo;
     uint64_t tile_mask;
     int32_t local_qubit[16];
+    TileRuns runs;
 };
 
 // Small states (kern_small.hip): the gates in circuit order; chunks of them

@@ -112,11 +112,6 @@ template <typename R>
 struct M4 {
     cx<R> e[16];
 };
-template <typename R>
-struct D4 {
-    cx<R> e[4];
-};
-
 // per-element selects on named values (no indexed access to a private array)
 template <typename R>
 __device__ __forceinline__ cx<R> sel(bool c, cx<R> x, cx<R> y) {
@@ -374,21 +369,60 @@ __device__ __forceinline__ Regs<R, NB> app_cx(Regs<R, NB> a, int rc, int tb) {
     return a;
 }
 
-// diagonal on one bit (d.e[0], d.e[1]) or two bits (d.e[2 b0 + b1])
+// diagonal (d0, d1) on a thread bit: one factor per lane
 template <typename R, int NB>
-__device__ __forceinline__ Regs<R, NB> app_diag(Regs<R, NB> a, int r0, int tb0, int r1, int tb1, bool two, D4<R> d) {
+__device__ __forceinline__ Regs<R, NB> app_diag_thread(Regs<R, NB> a, cx<R> f) {
 #pragma unroll
     for (int j = 0; j < NB; ++j) {
-        const int b0 = r0 >= 0 ? ((j >> r0) & 1) : tb0;
-        const int b1 = r1 >= 0 ? ((j >> r1) & 1) : tb1;
-        cx<R> f;
-        if (two) {
-            const cx<R> lo = sel(b1 != 0, d.e[1], d.e[0]), hi = sel(b1 != 0, d.e[3], d.e[2]);
-            f = sel(b0 != 0, hi, lo);
-        } else {
-            f = sel(b0 != 0, d.e[1], d.e[0]);
-        }
-        a.v[j] = a.v[j] * f;
+        const cx<R> x = a.v[j];
+        a.v[j] = {fmaR(x.re, f.re, -(x.im * f.im)), fmaR(x.im, f.re, x.re * f.im)};
+    }
+    return a;
+}
+
+// Two-qubit diagonals with run-time bits: which amplitudes of the block a pair of
+// register bits selects is one uniform mask over the block, a thread bit is one
+// value per lane, and a sign is one XOR, so there is one copy of the code and no
+// choice per amplitude.  (Selecting each amplitude's entry from the diagonal took
+// 14 instructions an amplitude where the product takes 4.)
+//
+// bit j of the result: bit r of j (r < 0: a thread bit, `none` instead)
+__device__ __forceinline__ uint32_t bits_of(int r, uint32_t none) {
+    uint32_t m = none;
+    m = r == 0 ? 0xAAAAAAAAu : m;
+    m = r == 1 ? 0xCCCCCCCCu : m;
+    m = r == 2 ? 0xF0F0F0F0u : m;
+    m = r == 3 ? 0xFF00FF00u : m;
+    m = r == 4 ? 0xFFFF0000u : m;
+    return m;
+}
+// v, or -v where bit = 1
+__device__ __forceinline__ float flip_sign(float v, uint32_t bit) {
+    return __uint_as_float(__float_as_uint(v) ^ (bit << 31));
+}
+__device__ __forceinline__ double flip_sign(double v, uint32_t bit) {
+    const unsigned long long b = (unsigned long long)__double_as_longlong(v);
+    return __longlong_as_double((long long)(b ^ ((unsigned long long)(bit << 31) << 32)));
+}
+// RZZ: amplitude j times c + i s, or times c - i s where bit j of `odd` is set
+// (the roundings written out: the imaginary part rounds x.re s first)
+template <typename R, int NB>
+__device__ __forceinline__ Regs<R, NB> app_zz(Regs<R, NB> a, uint32_t odd, R c, R s) {
+#pragma unroll
+    for (int j = 0; j < NB; ++j) {
+        const R f = flip_sign(s, (odd >> j) & 1u);
+        const cx<R> x = a.v[j];
+        a.v[j] = {fmaR(x.re, c, -(x.im * f)), fmaR(x.im, c, x.re * f)};
+    }
+    return a;
+}
+// CZ: amplitude j negated where bit j of `both` is set and the lane's `on` is 1
+template <typename R, int NB>
+__device__ __forceinline__ Regs<R, NB> app_cz(Regs<R, NB> a, uint32_t both, uint32_t on) {
+#pragma unroll
+    for (int j = 0; j < NB; ++j) {
+        const uint32_t neg = on & ((both >> j) & 1u);
+        a.v[j] = {flip_sign(a.v[j].re, neg), flip_sign(a.v[j].im, neg)};
     }
     return a;
 }
@@ -433,14 +467,13 @@ __device__ __forceinline__ R grad_rot1(int kind, Regs<R, NB> l, Regs<R, NB> p) {
     return g;
 }
 
-// RZ / RZZ: sum_j sign_j Im(conj(l_j) p_j), sign = (-1)^{bit} resp. (-1)^{b0 ^ b1}
-template <typename R, int NB>
-__device__ __forceinline__ R grad_zdiag(Regs<R, NB> l, Regs<R, NB> p, int r0, int tb0, int r1, int tb1) {
+// RZZ: sum_j sign_j Im(conj(l_j) p_j), sign = (-1)^{b0 ^ b1} over the register bits B0, B1 (-1: none)
+template <typename R, int NB, int B0, int B1>
+__device__ __forceinline__ R grad_zz(const Regs<R, NB>& l, const Regs<R, NB>& p) {
     R gp = R(0), gm = R(0);
 #pragma unroll
     for (int j = 0; j < NB; ++j) {
-        const int b0 = r0 >= 0 ? ((j >> r0) & 1) : tb0;
-        const int b1 = r1 >= 0 ? ((j >> r1) & 1) : tb1;
+        const int b0 = B0 >= 0 ? (j >> (B0 < 0 ? 0 : B0)) & 1 : 0, b1 = B1 >= 0 ? (j >> (B1 < 0 ? 0 : B1)) & 1 : 0;
         const R v = fmaR(l.v[j].re, p.v[j].im, -l.v[j].im * p.v[j].re);
         if (b0 ^ b1) gm += v;
         else gp += v;

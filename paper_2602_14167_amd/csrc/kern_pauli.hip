@@ -85,17 +85,6 @@ template <> __device__ __forceinline__ float grp_im<float>(const PGroup& G) { re
 template <> __device__ __forceinline__ double grp_re<double>(const PGroup& G) { return G.cbr; }
 template <> __device__ __forceinline__ double grp_im<double>(const PGroup& G) { return G.cbi; }
 
-__device__ __forceinline__ uint64_t tile_base(uint64_t tile, uint64_t tmask, int n) {
-    uint64_t base = 0;
-    int k = 0;
-    for (int q = 0; q < n; ++q) {
-        if ((tmask >> q) & 1) continue;
-        base |= ((tile >> k) & 1) << q;
-        ++k;
-    }
-    return base;
-}
-
 __device__ __forceinline__ double shfl_sum(double v, int width) {
     for (int o = width >> 1; o > 0; o >>= 1) v += __shfl_xor(v, o, width);
     return v;
@@ -166,7 +155,6 @@ k_pauli_tile(const JobList jl, const Job single) {
     const int wg = uniform(int(local - b * wgs));
     cptr<PPass> P = as_const(J.ppasses) + pass_idx;
     const int m = P->m, lo = P->lo;
-    const uint64_t tmask = P->tile_mask;
     int lq[MAX_TILE_BITS];
 #pragma unroll
     for (int i = 0; i < MAX_TILE_BITS; ++i) lq[i] = P->local_qubit[i];
@@ -195,7 +183,7 @@ k_pauli_tile(const JobList jl, const Job single) {
     constexpr int CW = CH / 4;   // packed parity-count words (a byte per element)
     static_assert(NB % CH == 0 && CH % 4 == 0, "chunks of whole count words");
     for (int64_t tile = wg; tile < tiles_per_state; tile += wgs) {
-        const uint64_t base = uniform64(int64_t(tile_base(uint64_t(tile), tmask, n)));
+        const uint64_t base = uniform64(int64_t(runs_base(uint64_t(tile), &P->runs)));
         __syncthreads();
         // psi tile -> LDS; element l = it*nt + t (lane-consecutive, coalesced)
         if (active) {

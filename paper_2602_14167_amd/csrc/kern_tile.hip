@@ -46,18 +46,6 @@ __device__ __forceinline__ uint64_t loc2glob(uint32_t l, int lo, int m, const in
     return g;
 }
 
-// tile base: the tile index's bits deposited into the qubits outside the tile
-__device__ __forceinline__ uint64_t tile_base(uint64_t tile, uint64_t tmask, int n) {
-    uint64_t base = 0;
-    int k = 0;
-    for (int q = 0; q < n; ++q) {
-        if ((tmask >> q) & 1) continue;
-        base |= ((tile >> k) & 1) << q;
-        ++k;
-    }
-    return base;
-}
-
 // LDS position of local index l: XOR-swizzle bits 1..3 with bits 5..7 so that
 // strided register reads spread over banks; bit 0 is untouched so 16-byte
 // pairs of complex64 stay adjacent.
@@ -106,47 +94,132 @@ __device__ __forceinline__ PassInfo read_pass(cptr<Pass> P) {
     return pi;
 }
 
-// HBM -> LDS (coalesced: lane-consecutive 16-byte chunks of local index space)
-template <typename R, int RB>
-__device__ __forceinline__ void tile_load(cx<R>* lds, gptr<const cx<R>> psi, uint64_t base, const PassInfo& pi, int t,
-                                          int nt) {
-    constexpr int VN = V16<R>::N;
-    const int iters = (1 << RB) / VN;
-    const uint64_t off_t = loc2glob(uint32_t(t * VN), pi.lo, pi.m, pi.lq);
-    cx<R> v[(1 << RB)];
+// `pin` passes a value through an empty asm statement: the compiler cannot
+// hoist what is computed from it out of the loop it sits in, nor share it
+// between two uses (shared or hoisted, the LDS and global addresses of a
+// tile's elements stay live across the whole sweep, and the reverse sweep
+// needs 370 registers); it costs no instruction.
+__device__ __forceinline__ uint64_t pin(uint64_t v) {
+    uint32_t lo = uint32_t(v), hi = uint32_t(v >> 32);
+    asm volatile("" : "+v"(lo), "+v"(hi));
+    return (uint64_t(hi) << 32) | lo;
+}
+__device__ __forceinline__ uint32_t pin(uint32_t v) {
+    asm volatile("" : "+v"(v));
+    return v;
+}
+
+template <typename T>
+__device__ __forceinline__ T& lds_at(T* lds, uint32_t byte) {
+    return *reinterpret_cast<T*>(reinterpret_cast<char*>(lds) + byte);
+}
+template <typename T>
+__device__ __forceinline__ const T& lds_at(const T* lds, uint32_t byte) {
+    return *reinterpret_cast<const T*>(reinterpret_cast<const char*>(lds) + byte);
+}
+
+// Tile addressing.  A thread's 2^QR amplitudes are VN = 2
+// (complex64) or 1 (complex128) amplitudes per 16-byte access: element it of
+// thread t is local index it * VN nt + VN t (+ k, k < VN).  The bits of it are
+// the top EB = QR - log2(VN) local bits, so its global offset is a
+// compile-time sum of their images hb[k] (per pass, uniform), and the
+// thread's part off_t is computed once (and pinned per use).
+template <typename R, int QR>
+struct QTileAddr {
+    static constexpr int VN = V16<R>::N;
+    static constexpr int EB = QR - (VN == 2 ? 1 : 0);
+    uint64_t hb[EB];       // global offsets of the element-index bits (uniform)
+    uint64_t off_t;        // the thread's part
+    uint32_t lsw_t;        // LDS byte offset: swz(VN t)
+    uint32_t lhb[EB];      // and swz of the element-index bits (uniform)
+};
+
+template <typename R, int QR, int ES>
+__device__ __forceinline__ QTileAddr<R, QR> q_tile_addr(const PassInfo& pi, int t) {
+    using A_t = QTileAddr<R, QR>;
+    A_t A;
+    const int b0 = pi.m - A_t::EB;   // first local bit of the element index
 #pragma unroll
-    for (int it = 0; it < iters; ++it) {
-        const uint32_t e0 = uint32_t(it * nt * VN);
-        const uint64_t g = base + loc2glob(e0, pi.lo, pi.m, pi.lq) + off_t;
-        V16<R>::load(psi + g, &v[it * VN]);
+    for (int k = 0; k < A_t::EB; ++k) {
+        int q = b0 + k;
+#pragma unroll
+        for (int i = 0; i < MAX_TILE_BITS; ++i)
+            if (i == b0 + k) q = pi.lq[i];
+        A.hb[k] = uint64_t(1) << q;
+        A.lhb[k] = swz(1u << (b0 + k)) * ES;
     }
+    A.off_t = loc2glob(uint32_t(t * A_t::VN), pi.lo, pi.m, pi.lq);
+    A.lsw_t = swz(uint32_t(t * A_t::VN)) * ES;
+    return A;
+}
+
+// (it is a constant once the loops over elements are unrolled: the selects fold)
+template <typename R, int QR>
+__device__ __forceinline__ uint64_t q_goff(const QTileAddr<R, QR>& A, int it) {
+    uint64_t g = 0;
 #pragma unroll
-    for (int it = 0; it < iters; ++it) {
-        const uint32_t e = uint32_t((it * nt + t) * VN);
+    for (int k = 0; k < QTileAddr<R, QR>::EB; ++k)
+        if ((it >> k) & 1) g += A.hb[k];
+    return g;
+}
+template <typename R, int QR>
+__device__ __forceinline__ uint32_t q_loff(const QTileAddr<R, QR>& A, int it) {
+    uint32_t a = 0;
 #pragma unroll
-        for (int k = 0; k < VN; ++k) lds[swz(e + k)] = v[it * VN + k];
+    for (int k = 0; k < QTileAddr<R, QR>::EB; ++k)
+        if ((it >> k) & 1) a ^= A.lhb[k];
+    return a;
+}
+
+// HBM -> registers (the loads stay in flight until the registers are used)
+// and registers -> LDS, separately, so that a tile can be fetched while
+// another one is processed
+template <typename R, int QR>
+struct QTileRegs {
+    cx<R> v[1 << QR];
+};
+
+template <typename R, int QR>
+__device__ __forceinline__ QTileRegs<R, QR> q_tile_fetch(gptr<const cx<R>> psi, uint64_t base,
+                                                         const QTileAddr<R, QR>& A) {
+    constexpr int VN = V16<R>::N;
+    const gptr<const cx<R>> p = psi + pin(A.off_t);
+    QTileRegs<R, QR> r;
+#pragma unroll
+    for (int it = 0; it < (1 << QR) / VN; ++it) V16<R>::load(p + (base + q_goff<R, QR>(A, it)), &r.v[it * VN]);
+    return r;
+}
+
+// (swz leaves bit 0 alone: the VN amplitudes of an access stay adjacent)
+template <typename R, int QR>
+__device__ __forceinline__ void q_tile_put(cx<R>* lds, const QTileRegs<R, QR>& r, const QTileAddr<R, QR>& A) {
+    constexpr int VN = V16<R>::N;
+    const uint32_t lt = pin(A.lsw_t);
+#pragma unroll
+    for (int it = 0; it < (1 << QR) / VN; ++it) {
+        const uint32_t e = lt ^ q_loff<R, QR>(A, it);
+#pragma unroll
+        for (int k = 0; k < VN; ++k) lds_at(lds, e ^ uint32_t(k * sizeof(cx<R>))) = r.v[it * VN + k];
     }
 }
 
-// flip: the tile holds -psi (shear rotations taken as -R(a - pi)); stored negated
-template <typename R, int RB>
-__device__ __forceinline__ void tile_store(const cx<R>* lds, gptr<cx<R>> psi, uint64_t base, const PassInfo& pi, int t,
-                                           int nt, bool flip) {
+template <typename R, int QR>
+__device__ __forceinline__ void q_tile_store(const cx<R>* lds, gptr<cx<R>> psi, uint64_t base,
+                                             const QTileAddr<R, QR>& A, bool flip) {
     constexpr int VN = V16<R>::N;
-    const int iters = (1 << RB) / VN;
-    const uint64_t off_t = loc2glob(uint32_t(t * VN), pi.lo, pi.m, pi.lq);
+    const gptr<cx<R>> p = psi + pin(A.off_t);
+    const uint32_t lt = pin(A.lsw_t);
     const R sg = flip ? R(-1) : R(1);
 #pragma unroll
-    for (int it = 0; it < iters; ++it) {
-        const uint32_t e = uint32_t((it * nt + t) * VN);
+    for (int it = 0; it < (1 << QR) / VN; ++it) {
+        const uint32_t e = lt ^ q_loff<R, QR>(A, it);
         cx<R> v[VN];
 #pragma unroll
         for (int k = 0; k < VN; ++k) {
-            v[k] = lds[swz(e + k)];
+            v[k] = lds_at(lds, e ^ uint32_t(k * sizeof(cx<R>)));
             if (flip) v[k] = {sg * v[k].re, sg * v[k].im};
         }
-        const uint64_t g = base + loc2glob(uint32_t(it * nt * VN), pi.lo, pi.m, pi.lq) + off_t;
-        V16<R>::store(psi + g, v);
+        V16<R>::store(p + (base + q_goff<R, QR>(A, it)), v);
     }
 }
 
@@ -161,22 +234,14 @@ struct PhaseMap {
 };
 
 template <int RB>
-__device__ __forceinline__ PhaseMap phase_map(cptr<Phase> F, int t, int m) {
+__device__ __forceinline__ PhaseMap phase_map(cptr<Phase> F, int t) {
     PhaseMap pm;
-    uint32_t rmask = 0;
 #pragma unroll
-    for (int i = 0; i < RB; ++i) {
-        pm.rbit[i] = 1u << F->R[i];
-        rmask |= pm.rbit[i];
-    }
-    // deposit the thread index into the non-register local bits
+    for (int i = 0; i < RB; ++i) pm.rbit[i] = 1u << F->R[i];
+    // the thread's bits at the non-register local bits, listed by the planner
     uint32_t tp = 0;
-    int k = 0;
-    for (int b = 0; b < m; ++b) {
-        if ((rmask >> b) & 1) continue;
-        tp |= uint32_t((t >> k) & 1) << b;
-        ++k;
-    }
+#pragma unroll
+    for (int k = 0; k < QTHR; ++k) tp |= ((uint32_t(t) >> k) & 1u) << F->tb[k];
     pm.tpart = tp;
     pm.tsw = swz(tp);
     return pm;
@@ -343,6 +408,29 @@ __device__ __forceinline__ R grad_rot1_at(int kind, int r, Regs<R, (1 << RB)> l,
     }
     return g;
 }
+// the register bits' part of the RZZ derivative (a thread bit only sets its sign)
+template <typename R, int RB>
+__device__ __forceinline__ R grad_zz_at(int r0, int r1, const Regs<R, (1 << RB)>& l, const Regs<R, (1 << RB)>& p) {
+    const int lo = r0 < r1 ? r0 : r1, hi = r0 < r1 ? r1 : r0;
+    if (hi < 0) return grad_zz<R, (1 << RB), -1, -1>(l, p);
+    R g = R(0);
+    if (lo < 0) {
+        switch (hi) {
+#define C1(B) case B: if constexpr (B < RB) g = grad_zz<R, (1 << RB), B, -1>(l, p); break;
+            TCNG_SINGLES(C1)
+#undef C1
+            default: break;
+        }
+        return g;
+    }
+    switch (lo * 8 + hi) {
+#define C2(B0, B1) case B0 * 8 + B1: if constexpr (B0 < B1 && B1 < RB) g = grad_zz<R, (1 << RB), B0, B1>(l, p); break;
+        TCNG_PAIRS(C2)
+#undef C2
+        default: break;
+    }
+    return g;
+}
 template <typename R, int RB>
 __device__ __forceinline__ void grad_fsim_at(int r0, int r1, Regs<R, (1 << RB)> l, Regs<R, (1 << RB)> p, R& gt,
                                              R& gp) {
@@ -427,11 +515,7 @@ __device__ __forceinline__ Regs<R, (1 << RB)> apply_op(Regs<R, (1 << RB)> a, con
             if (op.r0 >= 0) {
                 a = diag1r_at<R, RB>(a, op.r0, d0, d1);
             } else {
-                D4<R> d;
-                d.e[0] = d0;
-                d.e[1] = d1;
-                d.e[2] = d.e[3] = d0;
-                a = app_diag<R, (1 << RB)>(a, -1, tb0, -1, 0, false, d);
+                a = app_diag_thread<R, (1 << RB)>(a, sel(tb0 != 0, d1, d0));
             }
             break;
         }
@@ -448,13 +532,15 @@ __device__ __forceinline__ Regs<R, (1 << RB)> apply_op(Regs<R, (1 << RB)> a, con
             break;
         }
         default: {   // OP_DIAG2
-            D4<R> d;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const cx<R> w = om[i];
-                d.e[i] = INV ? conj(w) : w;
+            if (op.kind == K_CZ) {
+                const uint32_t on = (op.r0 >= 0 ? 1u : uint32_t(tb0)) & (op.r1 >= 0 ? 1u : uint32_t(tb1));
+                a = app_cz<R, (1 << RB)>(a, bits_of(op.r0, ~0u) & bits_of(op.r1, ~0u), on);
+            } else {   // RZZ: (c, s) = e^{-it/2} where the bits agree, the conjugate elsewhere
+                const cx<R> w = om[0];
+                const uint32_t odd = uint32_t(op.r0 >= 0 ? 0 : tb0) ^ uint32_t(op.r1 >= 0 ? 0 : tb1);
+                a = app_zz<R, (1 << RB)>(a, bits_of(op.r0, 0u) ^ bits_of(op.r1, 0u), w.re,
+                                         flip_sign(INV ? -w.im : w.im, odd));
             }
-            a = app_diag<R, (1 << RB)>(a, op.r0, tb0, op.r1, tb1, true, d);
             break;
         }
     }
@@ -538,22 +624,22 @@ k_tile_fwd(const JobList jl, const Job single) {
     const int t = threadIdx.x;
     // nt is a multiple of 64: whole waves are active or idle
     const bool active = uniform(t >> 6) < (nt >> 6);
-    const int64_t b = local / J.tiles;
-    const uint64_t tile = uint64_t(local - b * J.tiles);
-    const int n = J.n;
+    const int64_t b = local >> (J.n - pi.m);   // 2^(n - m) tiles per member
+    const uint64_t tile = uint64_t(local) & (uint64_t(J.tiles) - 1);
     gptr<cx<R>> psi = as_global(static_cast<cx<R>*>(J.state)) + b * J.stride;
     cptr<cx<R>> om = as_const(static_cast<const cx<R>*>(J.opm)) + size_t(b) * J.n_gates * 16;
     cptr<Phase> phases = as_const(J.phases);
     cptr<Op> ops = as_const(J.ops);
-    const uint64_t base = tile_base(tile, pi.tmask, n);
+    const uint64_t base = runs_base(tile, &P->runs);
     const int f_end = P->phase_end;
+    const QTileAddr<R, RB> A = q_tile_addr<R, RB, int(sizeof(cx<R>))>(pi, t);
 
-    if (active) tile_load<R, RB>(lds, psi, base, pi, t, nt);
+    if (active) q_tile_put<R, RB>(lds, q_tile_fetch<R, RB>(psi, base, A), A);
     __syncthreads();
     bool flip = false;
     for (int f = P->phase_begin; f < f_end; ++f) {
         if (active) {
-            const PhaseMap pm = phase_map<RB>(phases + f, t, pi.m);
+            const PhaseMap pm = phase_map<RB>(phases + f, t);
             Regs<R, (1 << RB)> a = regs_from_lds<R, RB>(lds, pm);
             const int o_end = phases[f].op_end;
             for (int o = phases[f].op_begin; o < o_end; ++o) {
@@ -564,7 +650,7 @@ k_tile_fwd(const JobList jl, const Job single) {
         }
         __syncthreads();
     }
-    if (active) tile_store<R, RB>(lds, psi, base, pi, t, nt, flip);
+    if (active) q_tile_store<R, RB>(lds, psi, base, A, flip);
 }
 
 // accumulate a thread's gradient partial into the wave's slot (float64).  The
@@ -613,20 +699,21 @@ k_tile_rev(const JobList jl, const Job single) {
 
     for (int i = t; i < nslots * nwaves; i += blockDim.x) red[i] = 0.0;
     // (the first __syncthreads below orders these writes before any accumulation)
+    const QTileAddr<R, RB> A = q_tile_addr<R, RB, int(sizeof(cx<R>))>(pi, t);
 
     for (int64_t tile = wg; tile < J.tiles; tile += wgs) {
-        const uint64_t base = tile_base(uint64_t(tile), pi.tmask, n);
+        const uint64_t base = runs_base(uint64_t(tile), &P->runs);
         // phases run backwards; psi and lambda take turns in the one LDS tile
         int f = f_last;
-        PhaseMap pm = phase_map<RB>(rphases + f, t, pi.m);
+        PhaseMap pm = phase_map<RB>(rphases + f, t);
         Blk ps, la;
         bool flip = false, flip_l = false;   // equal: psi and lambda see the same ops
         __syncthreads();
-        if (active) tile_load<R, RB>(lds, psi, base, pi, t, nt);
+        if (active) q_tile_put<R, RB>(lds, q_tile_fetch<R, RB>(psi, base, A), A);
         __syncthreads();
         if (active) ps = regs_from_lds<R, RB>(lds, pm);
         __syncthreads();
-        if (active) tile_load<R, RB>(lds, lam, base, pi, t, nt);
+        if (active) q_tile_put<R, RB>(lds, q_tile_fetch<R, RB>(lam, base, A), A);
         __syncthreads();
         if (active) la = regs_from_lds<R, RB>(lds, pm);
         for (;;) {
@@ -656,10 +743,9 @@ k_tile_rev(const JobList jl, const Job single) {
                         } else {                            // RZZ
                             const int tb0 = op.lb0 >= 0 ? int((pm.tpart >> op.lb0) & 1) : 0;
                             const int tb1 = op.lb1 >= 0 ? int((pm.tpart >> op.lb1) & 1) : 0;
-                            red_add(red, slot,
-                                    grad_zdiag<R, (1 << RB)>(la, ps, op.r0, tb0, op.type == OP_DIAG2 ? op.r1 : -1,
-                                                             op.type == OP_DIAG2 ? tb1 : 0),
-                                    lane);
+                            const bool odd = ((op.r0 >= 0 ? 0 : tb0) ^ (op.r1 >= 0 ? 0 : tb1)) != 0;
+                            const R v = grad_zz_at<R, RB>(op.r0, op.r1, la, ps);
+                            red_add(red, slot, odd ? -v : v, lane);
                         }
                     }
                     ps = apply_op<R, RB, true>(ps, op, pm.tpart, m16, flip);
@@ -677,7 +763,7 @@ k_tile_rev(const JobList jl, const Job single) {
             }
             if (f == f_begin) break;
             // hand both blocks to the previous phase's register assignment
-            const PhaseMap pn = phase_map<RB>(rphases + (f - 1), t, pi.m);
+            const PhaseMap pn = phase_map<RB>(rphases + (f - 1), t);
             __syncthreads();
             if (active) regs_to_lds<R, RB>(ps, lds, pm);
             __syncthreads();
@@ -692,11 +778,11 @@ k_tile_rev(const JobList jl, const Job single) {
         __syncthreads();
         if (active) regs_to_lds<R, RB>(ps, lds, pm);
         __syncthreads();
-        if (active) tile_store<R, RB>(lds, psi, base, pi, t, nt, flip);
+        if (active) q_tile_store<R, RB>(lds, psi, base, A, flip);
         __syncthreads();
         if (active) regs_to_lds<R, RB>(la, lds, pm);
         __syncthreads();
-        if (active) tile_store<R, RB>(lds, lam, base, pi, t, nt, flip_l);
+        if (active) q_tile_store<R, RB>(lds, lam, base, A, flip_l);
     }
     __syncthreads();
     double* part = J.part + size_t(b) * J.total_slots * wgs;
@@ -710,21 +796,6 @@ k_tile_rev(const JobList jl, const Job single) {
 // ---------------------------------------------------------------------------
 // rounds (complex64: QR = 4 or 5 register bits; complex128: QR = 3 or 4; see QPhase)
 // ---------------------------------------------------------------------------
-// `pin` passes a value through an empty asm statement: the compiler cannot
-// hoist what is computed from it out of the loop it sits in, nor share it
-// between two uses (shared or hoisted, the LDS and global addresses of a
-// tile's elements stay live across the whole sweep, and the reverse sweep
-// needs 370 registers); it costs no instruction.
-__device__ __forceinline__ uint64_t pin(uint64_t v) {
-    uint32_t lo = uint32_t(v), hi = uint32_t(v >> 32);
-    asm volatile("" : "+v"(lo), "+v"(hi));
-    return (uint64_t(hi) << 32) | lo;
-}
-__device__ __forceinline__ uint32_t pin(uint32_t v) {
-    asm volatile("" : "+v"(v));
-    return v;
-}
-
 template <typename R, int QR>
 using QBlk = Regs<R, (1 << QR)>;
 
@@ -781,15 +852,6 @@ __device__ __forceinline__ uint32_t qaddr(const QMap<QR>& q, int j) {
         if ((j >> i) & 1) a ^= MAPPED ? q.crsw[i] : q.rsw[i];
     return a;
 }
-template <typename T>
-__device__ __forceinline__ T& lds_at(T* lds, uint32_t byte) {
-    return *reinterpret_cast<T*>(reinterpret_cast<char*>(lds) + byte);
-}
-template <typename T>
-__device__ __forceinline__ const T& lds_at(const T* lds, uint32_t byte) {
-    return *reinterpret_cast<const T*>(reinterpret_cast<const char*>(lds) + byte);
-}
-
 // (each call forms its addresses anew: shared between calls, the compiler
 // keeps them all live in registers across the sweep)
 template <bool MAPPED, typename R, int QR>
@@ -890,111 +952,6 @@ struct QCoef {
     R c[QCOEF];
 };
 
-// Tile addressing of the rounds.  A thread's 2^QR amplitudes are VN = 2
-// (complex64) or 1 (complex128) amplitudes per 16-byte access: element it of
-// thread t is local index it * VN nt + VN t (+ k, k < VN).  The bits of it are
-// the top EB = QR - log2(VN) local bits, so its global offset is a
-// compile-time sum of their images hb[k] (per pass, uniform), and the
-// thread's part off_t is computed once (and pinned per use).
-template <typename R, int QR>
-struct QTileAddr {
-    static constexpr int VN = V16<R>::N;
-    static constexpr int EB = QR - (VN == 2 ? 1 : 0);
-    uint64_t hb[EB];       // global offsets of the element-index bits (uniform)
-    uint64_t off_t;        // the thread's part
-    uint32_t lsw_t;        // LDS byte offset: swz(VN t)
-    uint32_t lhb[EB];      // and swz of the element-index bits (uniform)
-};
-
-template <typename R, int QR, int ES>
-__device__ __forceinline__ QTileAddr<R, QR> q_tile_addr(const PassInfo& pi, int t) {
-    using A_t = QTileAddr<R, QR>;
-    A_t A;
-    const int b0 = pi.m - A_t::EB;   // first local bit of the element index
-#pragma unroll
-    for (int k = 0; k < A_t::EB; ++k) {
-        int q = b0 + k;
-#pragma unroll
-        for (int i = 0; i < MAX_TILE_BITS; ++i)
-            if (i == b0 + k) q = pi.lq[i];
-        A.hb[k] = uint64_t(1) << q;
-        A.lhb[k] = swz(1u << (b0 + k)) * ES;
-    }
-    A.off_t = loc2glob(uint32_t(t * A_t::VN), pi.lo, pi.m, pi.lq);
-    A.lsw_t = swz(uint32_t(t * A_t::VN)) * ES;
-    return A;
-}
-
-// (it is a constant once the loops over elements are unrolled: the selects fold)
-template <typename R, int QR>
-__device__ __forceinline__ uint64_t q_goff(const QTileAddr<R, QR>& A, int it) {
-    uint64_t g = 0;
-#pragma unroll
-    for (int k = 0; k < QTileAddr<R, QR>::EB; ++k)
-        if ((it >> k) & 1) g += A.hb[k];
-    return g;
-}
-template <typename R, int QR>
-__device__ __forceinline__ uint32_t q_loff(const QTileAddr<R, QR>& A, int it) {
-    uint32_t a = 0;
-#pragma unroll
-    for (int k = 0; k < QTileAddr<R, QR>::EB; ++k)
-        if ((it >> k) & 1) a ^= A.lhb[k];
-    return a;
-}
-
-// HBM -> registers (the loads stay in flight until the registers are used)
-// and registers -> LDS, separately, so that a tile can be fetched while
-// another one is processed
-template <typename R, int QR>
-struct QTileRegs {
-    cx<R> v[1 << QR];
-};
-
-template <typename R, int QR>
-__device__ __forceinline__ QTileRegs<R, QR> q_tile_fetch(gptr<const cx<R>> psi, uint64_t base,
-                                                         const QTileAddr<R, QR>& A) {
-    constexpr int VN = V16<R>::N;
-    const gptr<const cx<R>> p = psi + pin(A.off_t);
-    QTileRegs<R, QR> r;
-#pragma unroll
-    for (int it = 0; it < (1 << QR) / VN; ++it) V16<R>::load(p + (base + q_goff<R, QR>(A, it)), &r.v[it * VN]);
-    return r;
-}
-
-// (swz leaves bit 0 alone: the VN amplitudes of an access stay adjacent)
-template <typename R, int QR>
-__device__ __forceinline__ void q_tile_put(cx<R>* lds, const QTileRegs<R, QR>& r, const QTileAddr<R, QR>& A) {
-    constexpr int VN = V16<R>::N;
-    const uint32_t lt = pin(A.lsw_t);
-#pragma unroll
-    for (int it = 0; it < (1 << QR) / VN; ++it) {
-        const uint32_t e = lt ^ q_loff<R, QR>(A, it);
-#pragma unroll
-        for (int k = 0; k < VN; ++k) lds_at(lds, e ^ uint32_t(k * sizeof(cx<R>))) = r.v[it * VN + k];
-    }
-}
-
-template <typename R, int QR>
-__device__ __forceinline__ void q_tile_store(const cx<R>* lds, gptr<cx<R>> psi, uint64_t base,
-                                             const QTileAddr<R, QR>& A, bool flip) {
-    constexpr int VN = V16<R>::N;
-    const gptr<cx<R>> p = psi + pin(A.off_t);
-    const uint32_t lt = pin(A.lsw_t);
-    const R sg = flip ? R(-1) : R(1);
-#pragma unroll
-    for (int it = 0; it < (1 << QR) / VN; ++it) {
-        const uint32_t e = lt ^ q_loff<R, QR>(A, it);
-        cx<R> v[VN];
-#pragma unroll
-        for (int k = 0; k < VN; ++k) {
-            v[k] = lds_at(lds, e ^ uint32_t(k * sizeof(cx<R>)));
-            if (flip) v[k] = {sg * v[k].re, sg * v[k].im};
-        }
-        V16<R>::store(p + (base + q_goff<R, QR>(A, it)), v);
-    }
-}
-
 // A step's derivative partials into their slots, all of them in one reduction:
 // lane l ends with partial l % N, its slot comes from the step's own table (one
 // load per lane; -1: absent), and each lane adds its sum, in float64, to the
@@ -1044,12 +1001,12 @@ __global__ void __launch_bounds__(1 << (q_tile_bits<R>() - QR)) k_rounds_fwd(con
 
     const QTileAddr<R, QR> A = q_tile_addr<R, QR, ES>(pi, t);
     QTileRegs<R, QR> nx;
-    if (wg < J.tiles) nx = q_tile_fetch<R, QR>(psi, tile_base(uint64_t(wg), pi.tmask, J.n), A);
+    if (wg < J.tiles) nx = q_tile_fetch<R, QR>(psi, runs_base(uint64_t(wg), &P->runs), A);
     for (int64_t tile = wg; tile < J.tiles; tile += wgs) {
-        const uint64_t base = tile_base(uint64_t(tile), pi.tmask, J.n);
+        const uint64_t base = runs_base(uint64_t(tile), &P->runs);
         __syncthreads();   // the previous tile's stores have read the LDS
         q_tile_put<R, QR>(lds, nx, A);
-        if (tile + wgs < J.tiles) nx = q_tile_fetch<R, QR>(psi, tile_base(uint64_t(tile + wgs), pi.tmask, J.n), A);
+        if (tile + wgs < J.tiles) nx = q_tile_fetch<R, QR>(psi, runs_base(uint64_t(tile + wgs), &P->runs), A);
         __syncthreads();
         bool flip = false;
         for (int f = Q.phase_begin; f < Q.phase_end; ++f) {
@@ -1124,7 +1081,7 @@ __global__ void __launch_bounds__(1 << (q_tile_bits<R>() - QR)) k_rounds_rev(con
     const QTileAddr<R, QR> A = q_tile_addr<R, QR, ES>(pi, t);
 
     for (int64_t tile = wg; tile < J.tiles; tile += wgs) {
-        const uint64_t base = tile_base(uint64_t(tile), pi.tmask, J.n);
+        const uint64_t base = runs_base(uint64_t(tile), &P->runs);
         int f = Q.phase_end - 1;
         QMap<QR> q = qmap<QR, ES>(phases + f, t);
         QBlk<R, QR> ps, la;

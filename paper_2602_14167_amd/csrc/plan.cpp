@@ -128,6 +128,8 @@ std::string plan_phases(const std::vector<tcng_gate>& gates, const std::vector<i
         for (int b = 0; b < MAX_TILE_BITS; ++b) reg_of_local[b] = -1;
         for (int b = 0; b < m; ++b)
             if ((R >> b) & 1) { F.R[ri] = b; reg_of_local[b] = ri; ++ri; }
+        for (int b = 0, k = 0; b < m && k < QTHR; ++b)
+            if (!((R >> b) & 1)) F.tb[k++] = b;
         F.op_begin = int(ops.size());
         for (int gi : ph) {
             const tcng_gate& g = gates[gi];
@@ -558,6 +560,7 @@ std::string plan_circuit(int n, const std::vector<tcng_gate>& gates, int n_param
         if (li != m) return "internal: tile size mismatch";
         for (int q = 0; q < lo; ++q)
             if (qubit_to_local[q] != q) return "internal: low qubits not contiguous";
+        P.runs = tile_runs(T, n);
 
         // ---- slots of this pass
         P.slot_base = out.total_slots;
@@ -1000,6 +1003,7 @@ std::string plan_pauli(int n, const std::vector<PauliTermHost>& terms, const Til
         P.m = m;
         P.lo = lo;
         P.tile_mask = T;
+        P.runs = tile_runs(T, n);
         int qubit_to_local[64];
         for (int q = 0; q < 64; ++q) qubit_to_local[q] = -1;
         for (int i = 0; i < 16; ++i) P.local_qubit[i] = -1;

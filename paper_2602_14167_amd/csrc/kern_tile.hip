@@ -669,8 +669,11 @@ __device__ __forceinline__ void red_add(double* red, int idx, R v, int lane) {
 // reverse pass (pass n_passes - 1 - step): psi and lambda, gradient slots
 // accumulated per wave in LDS; `wgs` workgroups per member loop over the tiles
 // ---------------------------------------------------------------------------
-template <typename R, int RB>
-__global__ void __launch_bounds__((MaxThreads<R, RB>::value))
+// WAVES: waves a SIMD that the registers have to leave room for.  Left free (1) the
+// kernel takes 166 registers, and one workgroup of 512 threads fits a compute unit;
+// held to 128 (4) two do, at the price of 73 registers kept in scratch memory.
+template <typename R, int RB, int WAVES>
+__global__ void __launch_bounds__((MaxThreads<R, RB>::value), WAVES)
 k_tile_rev(const JobList jl, const Job single) {
     __shared__ cx<R> lds[Tile<R>::ELEMS];
     __shared__ double red[RED_SLOTS * (NTHREADS / 64)];
@@ -1273,7 +1276,18 @@ hipError_t launch_tile_fwd(const JobList& jl, const Job& single, int64_t blocks,
 template <typename R, int RB>
 hipError_t launch_tile_rev(const JobList& jl, const Job& single, int64_t blocks, int nthreads, hipStream_t st) {
     if (blocks <= 0) return hipSuccess;
-    hipLaunchKernelGGL((k_tile_rev<R, RB>), dim3(unsigned(blocks)), dim3(nthreads), 0, st, jl, single);
+    // Two workgroups share a compute unit only where there are more of them than units
+    // (256), and it is the registers that part them only at 512 threads (a smaller
+    // tile's waves fit beside each other as they are).  Gradients of Ising layers:
+    // 8 x 20 qubits (2048 workgroups) 3.48 ms at WAVES 1 and 2.87 at 4, 1 x 22 (512)
+    // 2.03 and 1.67; 4 x 18 (128) 0.98 and 1.03, 64 x 12 (64) 0.42 and 0.43;
+    // complex128 4 x 20 (1024) 3.20 and 2.72, 4 x 18 (256) 0.92 and 1.02.
+    if constexpr (MaxThreads<R, RB>::value == 512)
+        if (nthreads == 512 && blocks > 256) {
+            hipLaunchKernelGGL((k_tile_rev<R, RB, 4>), dim3(unsigned(blocks)), dim3(nthreads), 0, st, jl, single);
+            return hipGetLastError();
+        }
+    hipLaunchKernelGGL((k_tile_rev<R, RB, 1>), dim3(unsigned(blocks)), dim3(nthreads), 0, st, jl, single);
     return hipGetLastError();
 }
 

@@ -51,3 +51,24 @@ def test_tiles(oracle_mod, n, dt, mode, kinds, comb):
     te, tg = TOL[dt]
     assert abs(E.item() - ref["E"]) <= te * S
     assert len(params) == 0 or np.max(np.abs(g.cpu().numpy()[0] - ref["grad"])) <= tg * S
+
+
+# 256 and 258 reverse workgroups: the last launch at one workgroup a compute unit, the
+# first at two
+@pytest.mark.parametrize("n,dt", [(14, "c64"), (13, "c128")])
+@pytest.mark.parametrize("batch", [128, 129])
+def test_reverse_occupancy(oracle_mod, n, dt, batch):
+    import paper_2602_14167_amd as P
+    r = np.random.default_rng(n)
+    gates, params, mats = W.random_circuit(n, 80, r, kinds=[W.RX, W.RY, W.RZ, W.RZZ, W.CZ, W.CNOT, W.FSIM, W.U1, W.U2])
+    codes, coeffs = W.random_pauli_sum(n, 10, r, max_weight=4)
+    circ, H = P.Circuit(n, gates, len(params), mats), P.PauliSum(n, codes, coeffs)
+    many = r.uniform(-np.pi, np.pi, (batch, len(params)))
+    E, g = P.expect_grad(circ, torch.as_tensor(many).to(device="cuda", dtype=RDT[dt]), H, dtype=TDT[dt],
+                         mode="tiled")
+    S = float(np.abs(coeffs).sum())
+    te, tg = TOL[dt]
+    for b in (0, batch // 2, batch - 1):
+        ref = oracle_mod.expect_grad(n, gates, W.round_params(many[b], dt), codes, coeffs, W.round_mats(mats, dt))
+        assert abs(E[b].item() - ref["E"]) <= te * S
+        assert np.max(np.abs(g.cpu().numpy()[b] - ref["grad"])) <= tg * S

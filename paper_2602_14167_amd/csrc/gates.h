@@ -158,19 +158,6 @@ __device__ __forceinline__ Regs<R, NB> app_real1(Regs<R, NB> a, R u0, R u1, R u2
     return a;
 }
 
-// [[c, -i s], [-i s, c]] on register bit B (RX with c = cos t/2, s = sin t/2)
-template <typename R, int NB, int B>
-__device__ __forceinline__ Regs<R, NB> app_rx(Regs<R, NB> a, R c, R s) {
-#pragma unroll
-    for (int j = 0; j < NB; ++j) {
-        if (j & (1 << B)) continue;
-        const cx<R> x0 = a.v[j], x1 = a.v[j | (1 << B)];
-        a.v[j] = {fmaR(s, x1.im, c * x0.re), fmaR(-s, x1.re, c * x0.im)};
-        a.v[j | (1 << B)] = {fmaR(s, x0.im, c * x1.re), fmaR(-s, x0.re, c * x1.im)};
-    }
-    return a;
-}
-
 // ---------------------------------------------------------------------------
 // Rotations by three shears.  A plane rotation
 //   R(a) = [[cos a, -sin a], [sin a, cos a]]
@@ -404,18 +391,6 @@ __device__ __forceinline__ double flip_sign(double v, uint32_t bit) {
     const unsigned long long b = (unsigned long long)__double_as_longlong(v);
     return __longlong_as_double((long long)(b ^ ((unsigned long long)(bit << 31) << 32)));
 }
-// RZZ: amplitude j times c + i s, or times c - i s where bit j of `odd` is set
-// (the roundings written out: the imaginary part rounds x.re s first)
-template <typename R, int NB>
-__device__ __forceinline__ Regs<R, NB> app_zz(Regs<R, NB> a, uint32_t odd, R c, R s) {
-#pragma unroll
-    for (int j = 0; j < NB; ++j) {
-        const R f = flip_sign(s, (odd >> j) & 1u);
-        const cx<R> x = a.v[j];
-        a.v[j] = {fmaR(x.re, c, -(x.im * f)), fmaR(x.im, c, x.re * f)};
-    }
-    return a;
-}
 // CZ: amplitude j negated where bit j of `both` is set and the lane's `on` is 1
 template <typename R, int NB>
 __device__ __forceinline__ Regs<R, NB> app_cz(Regs<R, NB> a, uint32_t both, uint32_t on) {
@@ -479,6 +454,20 @@ __device__ __forceinline__ R grad_zz(const Regs<R, NB>& l, const Regs<R, NB>& p)
         else gp += v;
     }
     return gp - gm;
+}
+
+// RZZ on register bits B0, B1 (-1: none, a thread bit's sign is in s already):
+// amplitude j times c + i s, or times c - i s where the bits differ (the roundings
+// written out: the imaginary part rounds x.re s first)
+template <typename R, int NB, int B0, int B1>
+__device__ __forceinline__ void app_zz(Regs<R, NB>& a, R c, R s) {
+#pragma unroll
+    for (int j = 0; j < NB; ++j) {
+        const int b0 = B0 >= 0 ? (j >> (B0 < 0 ? 0 : B0)) & 1 : 0, b1 = B1 >= 0 ? (j >> (B1 < 0 ? 0 : B1)) & 1 : 0;
+        const R f = (b0 ^ b1) ? -s : s;
+        const cx<R> x = a.v[j];
+        a.v[j] = {fmaR(x.re, c, -(x.im * f)), fmaR(x.im, c, x.re * f)};
+    }
 }
 
 // FSIM: theta -> 2 Im(conj(l01) p10 + conj(l10) p01), phi -> 2 Im(conj(l11) p11)

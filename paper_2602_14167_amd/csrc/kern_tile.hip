@@ -171,6 +171,14 @@ __device__ __forceinline__ uint32_t q_loff(const QTileAddr<R, QR>& A, int it) {
     return a;
 }
 
+// the same, with the sums of its parts to be formed again
+template <typename R, int QR>
+__device__ __forceinline__ QTileAddr<R, QR> fresh(QTileAddr<R, QR> A) {
+    A.off_t = pin(A.off_t);
+    A.lsw_t = pin(A.lsw_t);
+    return A;
+}
+
 // HBM -> registers (the loads stay in flight until the registers are used)
 // and registers -> LDS, separately, so that a tile can be fetched while
 // another one is processed
@@ -256,17 +264,23 @@ __device__ __forceinline__ uint32_t jpart(const PhaseMap& pm, int j) {
     return p;
 }
 
+// (in bytes, and the addresses formed anew each time: kept over the ops of a phase
+// they took 16 registers that the ops need)
 template <typename R, int RB>
-__device__ __forceinline__ Regs<R, (1 << RB)> regs_from_lds(const cx<R>* lds, const PhaseMap& pm) {
+__device__ __forceinline__ Regs<R, (1 << RB)> regs_from_lds(cx<R>* lds, const PhaseMap& pm) {
+    constexpr uint32_t ES = sizeof(cx<R>);
+    const uint32_t ts = pin(pm.tsw) * ES;
     Regs<R, (1 << RB)> a;
 #pragma unroll
-    for (int j = 0; j < (1 << RB); ++j) a.v[j] = lds[pm.tsw ^ swz(jpart<RB>(pm, j))];
+    for (int j = 0; j < (1 << RB); ++j) a.v[j] = lds_at(lds, ts ^ (swz(jpart<RB>(pm, j)) * ES));
     return a;
 }
 template <typename R, int RB>
 __device__ __forceinline__ void regs_to_lds(Regs<R, (1 << RB)> a, cx<R>* lds, const PhaseMap& pm) {
+    constexpr uint32_t ES = sizeof(cx<R>);
+    const uint32_t ts = pin(pm.tsw) * ES;
 #pragma unroll
-    for (int j = 0; j < (1 << RB); ++j) lds[pm.tsw ^ swz(jpart<RB>(pm, j))] = a.v[j];
+    for (int j = 0; j < (1 << RB); ++j) lds_at(lds, ts ^ (swz(jpart<RB>(pm, j)) * ES)) = a.v[j];
 }
 
 // ---------------------------------------------------------------------------
@@ -310,16 +324,6 @@ template <typename R, int RB>
 __device__ __forceinline__ Regs<R, (1 << RB)> real1_at(Regs<R, (1 << RB)> a, int r, R u0, R u1, R u2, R u3) {
     switch (r) {
 #define C1(B) case B: if constexpr (B < RB) a = app_real1<R, (1 << RB), B>(a, u0, u1, u2, u3); break;
-        TCNG_SINGLES(C1)
-#undef C1
-        default: break;
-    }
-    return a;
-}
-template <typename R, int RB>
-__device__ __forceinline__ Regs<R, (1 << RB)> rx_at(Regs<R, (1 << RB)> a, int r, R c, R s) {
-    switch (r) {
-#define C1(B) case B: if constexpr (B < RB) a = app_rx<R, (1 << RB), B>(a, c, s); break;
         TCNG_SINGLES(C1)
 #undef C1
         default: break;
@@ -397,39 +401,62 @@ __device__ __forceinline__ Regs<R, (1 << RB)> fsim_at(Regs<R, (1 << RB)> a, int 
     }
     return a;
 }
-template <typename R, int RB>
-__device__ __forceinline__ R grad_rot1_at(int kind, int r, Regs<R, (1 << RB)> l, Regs<R, (1 << RB)> p) {
+template <int B0_, int B1_>
+struct Bits {
+    static constexpr int B0 = B0_, B1 = B1_;
+};
+// what a reverse step does with an RX or RY on register bit r: the derivative (if
+// wanted) and the inverse rotation of both states, in one branch.  (The derivative
+// and each state's rotation were three dispatches on kind and bits, each rotation
+// with its own division for the shear: 323 vector and 198 scalar instructions and 51
+// branches an op where the arithmetic is 150.  Gradients of Ising layers, with the
+// RZZ taken the same way: 20 qubits x 8 3.48 -> 2.68 ms, 18 x 4 0.98 -> 0.78, 12 x 64
+// 0.42 -> 0.33; complex128 20 x 4 3.20 -> 2.49.  Held to 128 registers, for two
+// workgroups a compute unit, the kernel spills 147 of its 168: 3.55 ms.)
+template <typename R, int RB, int KIND>
+__device__ __forceinline__ R rev_rot1_at(int r, bool want, Regs<R, (1 << RB)>& l, Regs<R, (1 << RB)>& p, Lift<R> L) {
     R g = R(0);
     switch (r) {
-#define C1(B) case B: if constexpr (B < RB) g = grad_rot1<R, (1 << RB), B>(kind, l, p); break;
+#define C1(B)                                                                          \
+    case B:                                                                            \
+        if constexpr (B < RB) {                                                        \
+            if (want) g = grad_rot1<R, (1 << RB), B>(KIND, l, p);                      \
+            if constexpr (KIND == K_RX) {                                              \
+                p = app_rx_lift<R, (1 << RB), B>(p, L);                                \
+                l = app_rx_lift<R, (1 << RB), B>(l, L);                                \
+            } else {                                                                   \
+                p = app_ry_lift<R, (1 << RB), B>(p, L);                                \
+                l = app_ry_lift<R, (1 << RB), B>(l, L);                                \
+            }                                                                          \
+        }                                                                              \
+        break;
         TCNG_SINGLES(C1)
 #undef C1
         default: break;
     }
     return g;
 }
-// the register bits' part of the RZZ derivative (a thread bit only sets its sign)
-template <typename R, int RB>
-__device__ __forceinline__ R grad_zz_at(int r0, int r1, const Regs<R, (1 << RB)>& l, const Regs<R, (1 << RB)>& p) {
+// f(Bits<B0, B1>) for the register bits of an RZZ (-1: a thread bit)
+template <int RB, typename F>
+__device__ __forceinline__ void zz_at(int r0, int r1, F&& f) {
     const int lo = r0 < r1 ? r0 : r1, hi = r0 < r1 ? r1 : r0;
-    if (hi < 0) return grad_zz<R, (1 << RB), -1, -1>(l, p);
-    R g = R(0);
-    if (lo < 0) {
+    if (lo >= 0) {
+        switch (lo * 8 + hi) {
+#define C2(B0, B1) case B0 * 8 + B1: if constexpr (B0 < B1 && B1 < RB) f(Bits<B0, B1>{}); break;
+            TCNG_PAIRS(C2)
+#undef C2
+            default: break;
+        }
+    } else if (hi >= 0) {
         switch (hi) {
-#define C1(B) case B: if constexpr (B < RB) g = grad_zz<R, (1 << RB), B, -1>(l, p); break;
+#define C1(B) case B: if constexpr (B < RB) f(Bits<B, -1>{}); break;
             TCNG_SINGLES(C1)
 #undef C1
             default: break;
         }
-        return g;
+    } else {
+        f(Bits<-1, -1>{});
     }
-    switch (lo * 8 + hi) {
-#define C2(B0, B1) case B0 * 8 + B1: if constexpr (B0 < B1 && B1 < RB) g = grad_zz<R, (1 << RB), B0, B1>(l, p); break;
-        TCNG_PAIRS(C2)
-#undef C2
-        default: break;
-    }
-    return g;
 }
 template <typename R, int RB>
 __device__ __forceinline__ void grad_fsim_at(int r0, int r1, Regs<R, (1 << RB)> l, Regs<R, (1 << RB)> p, R& gt,
@@ -456,31 +483,29 @@ __device__ __forceinline__ void cot_u2_at(int r0, int r1, Regs<R, (1 << RB)> l, 
     }
 }
 
-// apply one op (forward, or its inverse when INV) to the register block;
-// om: the op's matrix entries for this batch member (k_build_ops)
-// RY, RX and RZ go through shear rotations and toggle `flip` (one sign per
-// state, see lift_of).
+// shear coefficients of an RX, RY or RZ (entries 4, 5 of its table: the division is
+// made once, in k_build_ops); toggles `flip` (one sign per state, see lift_of)
+template <typename R, bool INV>
+__device__ __forceinline__ Lift<R> lift_at(cptr<cx<R>> om, bool& flip) {
+    const cx<R> ts = om[4];
+    flip ^= om[5].re < R(0);
+    return INV ? Lift<R>{-ts.re, -ts.im} : Lift<R>{ts.re, ts.im};
+}
+// the sign that an operand which is a thread bit gives an RZZ (1: negative)
+__device__ __forceinline__ uint32_t zz_thread_sign(const Op& op, uint32_t tpart) {
+    const uint32_t tb0 = op.r0 >= 0 ? 0u : (tpart >> op.lb0) & 1u;
+    const uint32_t tb1 = op.r1 >= 0 ? 0u : (tpart >> op.lb1) & 1u;
+    return tb0 ^ tb1;
+}
+
+// apply one op (forward, or its inverse when INV) to the register block, by its
+// type; om: the op's matrix entries for this batch member (k_build_ops).
+// RX, RY, RZ and RZZ are not met here (apply_op, k_tile_rev).
 template <typename R, int RB, bool INV>
-__device__ __forceinline__ Regs<R, (1 << RB)> apply_op(Regs<R, (1 << RB)> a, const Op& op, uint32_t tpart,
-                                                      cptr<cx<R>> om, bool& flip) {
+__device__ __forceinline__ Regs<R, (1 << RB)> apply_mat(Regs<R, (1 << RB)> a, const Op& op, uint32_t tpart,
+                                                       cptr<cx<R>> om) {
     const int tb0 = op.lb0 >= 0 ? int((tpart >> op.lb0) & 1) : 0;
     const int tb1 = op.lb1 >= 0 ? int((tpart >> op.lb1) & 1) : 0;
-    if (op.kind == K_RY) {
-        const R c = om[0].re, s = om[2].re;
-        return ry_lift_at<R, RB>(a, op.r0, lift_of<R>(c, INV ? -s : s, flip));
-    }
-    if (op.kind == K_RX) {
-        const R c = om[0].re, s = -om[1].im;
-        return rx_lift_at<R, RB>(a, op.r0, lift_of<R>(c, INV ? -s : s, flip));
-    }
-    if (op.kind == K_RZ) {
-        // om[1] = c + i s: the phase of |1>
-        const R c = om[1].re, s = om[1].im;
-        const Lift<R> L = lift_of<R>(c, INV ? -s : s, flip);
-        if (op.r0 >= 0) return rz_lift_at<R, RB>(a, op.r0, L);
-        const R sg = tb0 ? R(1) : R(-1);
-        return app_phase_lift<R, (1 << RB)>(a, Lift<R>{sg * L.t, sg * L.s});
-    }
     switch (op.type) {
         case OP_DENSE1: {
             M2<R> u;
@@ -494,11 +519,6 @@ __device__ __forceinline__ Regs<R, (1 << RB)> apply_op(Regs<R, (1 << RB)> a, con
             // real orthogonal: the inverse is the transpose
             const R u0 = om[0].re, u1 = om[1].re, u2 = om[2].re, u3 = om[3].re;
             a = INV ? real1_at<R, RB>(a, op.r0, u0, u2, u1, u3) : real1_at<R, RB>(a, op.r0, u0, u1, u2, u3);
-            break;
-        }
-        case OP_RX: {
-            const R c = om[0].re, s = -om[1].im;
-            a = rx_at<R, RB>(a, op.r0, c, INV ? -s : s);
             break;
         }
         case OP_FSIM: {
@@ -531,20 +551,35 @@ __device__ __forceinline__ Regs<R, (1 << RB)> apply_op(Regs<R, (1 << RB)> a, con
             a = dense2_at<R, RB>(a, op.r0, op.r1, u);
             break;
         }
-        default: {   // OP_DIAG2
-            if (op.kind == K_CZ) {
-                const uint32_t on = (op.r0 >= 0 ? 1u : uint32_t(tb0)) & (op.r1 >= 0 ? 1u : uint32_t(tb1));
-                a = app_cz<R, (1 << RB)>(a, bits_of(op.r0, ~0u) & bits_of(op.r1, ~0u), on);
-            } else {   // RZZ: (c, s) = e^{-it/2} where the bits agree, the conjugate elsewhere
-                const cx<R> w = om[0];
-                const uint32_t odd = uint32_t(op.r0 >= 0 ? 0 : tb0) ^ uint32_t(op.r1 >= 0 ? 0 : tb1);
-                a = app_zz<R, (1 << RB)>(a, bits_of(op.r0, 0u) ^ bits_of(op.r1, 0u), w.re,
-                                         flip_sign(INV ? -w.im : w.im, odd));
-            }
+        default: {   // OP_DIAG2: CZ
+            const uint32_t on = (op.r0 >= 0 ? 1u : uint32_t(tb0)) & (op.r1 >= 0 ? 1u : uint32_t(tb1));
+            a = app_cz<R, (1 << RB)>(a, bits_of(op.r0, ~0u) & bits_of(op.r1, ~0u), on);
             break;
         }
     }
     return a;
+}
+
+// forward: apply one op to the register block
+template <typename R, int RB>
+__device__ __forceinline__ Regs<R, (1 << RB)> apply_op(Regs<R, (1 << RB)> a, const Op& op, uint32_t tpart,
+                                                      cptr<cx<R>> om, bool& flip) {
+    constexpr int NB = 1 << RB;
+    if (op.kind == K_RY) return ry_lift_at<R, RB>(a, op.r0, lift_at<R, false>(om, flip));
+    if (op.kind == K_RX) return rx_lift_at<R, RB>(a, op.r0, lift_at<R, false>(om, flip));
+    if (op.kind == K_RZ) {
+        const Lift<R> L = lift_at<R, false>(om, flip);
+        if (op.r0 >= 0) return rz_lift_at<R, RB>(a, op.r0, L);
+        const R sg = ((tpart >> op.lb0) & 1) ? R(1) : R(-1);
+        return app_phase_lift<R, NB>(a, Lift<R>{sg * L.t, sg * L.s});
+    }
+    if (op.kind == K_RZZ) {   // (c, s) = e^{-it/2} where the bits agree, the conjugate elsewhere
+        const cx<R> w = om[0];
+        const R s = flip_sign(w.im, zz_thread_sign(op, tpart));
+        zz_at<RB>(op.r0, op.r1, [&](auto B) { app_zz<R, NB, decltype(B)::B0, decltype(B)::B1>(a, w.re, s); });
+        return a;
+    }
+    return apply_mat<R, RB, false>(a, op, tpart, om);
 }
 
 // matrix entries of one op (table indexed by gate)
@@ -560,12 +595,12 @@ __device__ __forceinline__ void build_op(const Op& op, const R* prm, const cx<R>
         default: break;
     }
     int cnt = (op.type == OP_DENSE2 || op.type == OP_FSIM) ? 16 : (op.type == OP_CX ? 0 : 4);
-    if (op.kind == K_RY || op.kind == K_RZ) {
-        // shear coefficients for the rotation rounds: entry 4 = (t, s), entry 5 = (-1 if the
-        // rotation is taken as -R(a - pi), else 1; 0).  RY: cos, sin of a = theta / 2 in
-        // u[0], u[2]; RZ: the phase of |1> is u[1] = cos + i sin.
-        const R c = op.kind == K_RY ? u[0].re : u[1].re;
-        const R sn = op.kind == K_RY ? u[2].re : u[1].im;
+    if (op.kind == K_RX || op.kind == K_RY || op.kind == K_RZ) {
+        // shear coefficients: entry 4 = (t, s), entry 5 = (-1 if the rotation is taken as
+        // -R(a - pi), else 1; 0).  RY: cos, sin of a = theta / 2 in u[0], u[2]; RX: in
+        // u[0], -u[1].im; RZ: the phase of |1> is u[1] = cos + i sin.
+        const R c = op.kind == K_RZ ? u[1].re : u[0].re;
+        const R sn = op.kind == K_RY ? u[2].re : op.kind == K_RX ? -u[1].im : u[1].im;
         bool flip = false;
         const Lift<R> L = lift_of<R>(c, sn, flip);
         u[4] = {L.t, L.s};
@@ -644,7 +679,7 @@ k_tile_fwd(const JobList jl, const Job single) {
             const int o_end = phases[f].op_end;
             for (int o = phases[f].op_begin; o < o_end; ++o) {
                 const Op op = ops[o];
-                a = apply_op<R, RB, false>(a, op, pm.tpart, om + 16 * op.gate, flip);
+                a = apply_op<R, RB>(a, op, pm.tpart, om + 16 * op.gate, flip);
             }
             regs_to_lds<R, RB>(a, lds, pm);
         }
@@ -669,15 +704,13 @@ __device__ __forceinline__ void red_add(double* red, int idx, R v, int lane) {
 // reverse pass (pass n_passes - 1 - step): psi and lambda, gradient slots
 // accumulated per wave in LDS; `wgs` workgroups per member loop over the tiles
 // ---------------------------------------------------------------------------
-// WAVES: waves a SIMD that the registers have to leave room for.  Left free (1) the
-// kernel takes 166 registers, and one workgroup of 512 threads fits a compute unit;
-// held to 128 (4) two do, at the price of 73 registers kept in scratch memory.
-template <typename R, int RB, int WAVES>
-__global__ void __launch_bounds__((MaxThreads<R, RB>::value), WAVES)
+template <typename R, int RB>
+__global__ void __launch_bounds__((MaxThreads<R, RB>::value))
 k_tile_rev(const JobList jl, const Job single) {
     __shared__ cx<R> lds[Tile<R>::ELEMS];
     __shared__ double red[RED_SLOTS * (NTHREADS / 64)];
-    using Blk = Regs<R, (1 << RB)>;
+    constexpr int NB = 1 << RB;
+    using Blk = Regs<R, NB>;
     int64_t local;
     const Job J = load_job(jl, single, blockIdx.x, local);
     const int pidx = J.n_passes - 1 - jl.step;
@@ -710,7 +743,7 @@ k_tile_rev(const JobList jl, const Job single) {
         int f = f_last;
         PhaseMap pm = phase_map<RB>(rphases + f, t);
         Blk ps, la;
-        bool flip = false, flip_l = false;   // equal: psi and lambda see the same ops
+        bool flip = false;   // (psi's and lambda's: both see the same ops)
         __syncthreads();
         if (active) q_tile_put<R, RB>(lds, q_tile_fetch<R, RB>(psi, base, A), A);
         __syncthreads();
@@ -726,33 +759,53 @@ k_tile_rev(const JobList jl, const Job single) {
                     const Op op = rops[o];
                     cptr<cx<R>> m16 = om + 16 * op.gate;
                     const int slot = op.slot * nwaves + wave;
-                    if (op.slot >= 0 && op.kind != K_U2) {
-                        if (op.kind == K_RX || op.kind == K_RY) {
-                            red_add(red, slot, grad_rot1_at<R, RB>(op.kind, op.r0, la, ps), lane);
-                        } else if (op.kind == K_FSIM) {
-                            R gt, gp;
-                            grad_fsim_at<R, RB>(op.r0, op.r1, la, ps, gt, gp);
-                            red_add(red, slot, gt, lane);
-                            red_add(red, slot + nwaves, gp, lane);
-                        } else if (op.kind == K_RZ) {
-                            R g;
+                    const bool want = op.slot >= 0;
+                    if (op.kind == K_RX || op.kind == K_RY || op.kind == K_RZZ || op.kind == K_RZ) {
+                        R g = R(0);
+                        if (op.kind == K_RX) {
+                            g = rev_rot1_at<R, RB, K_RX>(op.r0, want, la, ps, lift_at<R, true>(m16, flip));
+                        } else if (op.kind == K_RY) {
+                            g = rev_rot1_at<R, RB, K_RY>(op.r0, want, la, ps, lift_at<R, true>(m16, flip));
+                        } else if (op.kind == K_RZZ) {
+                            const cx<R> w = m16[0];
+                            const uint32_t odd = zz_thread_sign(op, pm.tpart);
+                            const R s = flip_sign(-w.im, odd);
+                            zz_at<RB>(op.r0, op.r1, [&](auto B) {
+                                constexpr int B0 = decltype(B)::B0, B1 = decltype(B)::B1;
+                                if (want) g = grad_zz<R, NB, B0, B1>(la, ps);
+                                app_zz<R, NB, B0, B1>(ps, w.re, s);
+                                app_zz<R, NB, B0, B1>(la, w.re, s);
+                            });
+                            g = flip_sign(g, odd);
+                        } else {
+                            const Lift<R> L = lift_at<R, true>(m16, flip);
                             if (op.r0 >= 0) {
-                                g = grad_rz_at<R, RB>(op.r0, la, ps);
+                                if (want) g = grad_rz_at<R, RB>(op.r0, la, ps);
+                                ps = rz_lift_at<R, RB>(ps, op.r0, L);
+                                la = rz_lift_at<R, RB>(la, op.r0, L);
                             } else {
-                                const R v = sum_im_conj<R, (1 << RB)>(la, ps);
-                                g = ((pm.tpart >> op.lb0) & 1) ? -v : v;
+                                const bool one = ((pm.tpart >> op.lb0) & 1) != 0;
+                                const R sg = one ? R(1) : R(-1);
+                                const Lift<R> T{sg * L.t, sg * L.s};
+                                if (want) {
+                                    const R v = sum_im_conj<R, NB>(la, ps);
+                                    g = one ? -v : v;
+                                }
+                                ps = app_phase_lift<R, NB>(ps, T);
+                                la = app_phase_lift<R, NB>(la, T);
                             }
-                            red_add(red, slot, g, lane);
-                        } else {                            // RZZ
-                            const int tb0 = op.lb0 >= 0 ? int((pm.tpart >> op.lb0) & 1) : 0;
-                            const int tb1 = op.lb1 >= 0 ? int((pm.tpart >> op.lb1) & 1) : 0;
-                            const bool odd = ((op.r0 >= 0 ? 0 : tb0) ^ (op.r1 >= 0 ? 0 : tb1)) != 0;
-                            const R v = grad_zz_at<R, RB>(op.r0, op.r1, la, ps);
-                            red_add(red, slot, odd ? -v : v, lane);
                         }
+                        if (want) red_add(red, slot, g, lane);
+                        continue;
                     }
-                    ps = apply_op<R, RB, true>(ps, op, pm.tpart, m16, flip);
-                    if (op.kind == K_U2 && op.slot >= 0) {
+                    if (want && op.kind == K_FSIM) {
+                        R gt, gp;
+                        grad_fsim_at<R, RB>(op.r0, op.r1, la, ps, gt, gp);
+                        red_add(red, slot, gt, lane);
+                        red_add(red, slot + nwaves, gp, lane);
+                    }
+                    ps = apply_mat<R, RB, true>(ps, op, pm.tpart, m16);
+                    if (want && op.kind == K_U2) {
 #pragma unroll
                         for (int e = 0; e < 16; ++e) {
                             R gr, gi;
@@ -761,7 +814,7 @@ k_tile_rev(const JobList jl, const Job single) {
                             red_add(red, slot + (2 * e + 1) * nwaves, gi, lane);
                         }
                     }
-                    la = apply_op<R, RB, true>(la, op, pm.tpart, m16, flip_l);
+                    la = apply_mat<R, RB, true>(la, op, pm.tpart, m16);
                 }
             }
             if (f == f_begin) break;
@@ -781,11 +834,12 @@ k_tile_rev(const JobList jl, const Job single) {
         __syncthreads();
         if (active) regs_to_lds<R, RB>(ps, lds, pm);
         __syncthreads();
-        if (active) q_tile_store<R, RB>(lds, psi, base, A, flip);
+        const QTileAddr<R, RB> S = fresh(A);   // (not the loads' addresses kept over the ops)
+        if (active) q_tile_store<R, RB>(lds, psi, base, S, flip);
         __syncthreads();
         if (active) regs_to_lds<R, RB>(la, lds, pm);
         __syncthreads();
-        if (active) q_tile_store<R, RB>(lds, lam, base, A, flip_l);
+        if (active) q_tile_store<R, RB>(lds, lam, base, S, flip);
     }
     __syncthreads();
     double* part = J.part + size_t(b) * J.total_slots * wgs;
@@ -1276,18 +1330,7 @@ hipError_t launch_tile_fwd(const JobList& jl, const Job& single, int64_t blocks,
 template <typename R, int RB>
 hipError_t launch_tile_rev(const JobList& jl, const Job& single, int64_t blocks, int nthreads, hipStream_t st) {
     if (blocks <= 0) return hipSuccess;
-    // Two workgroups share a compute unit only where there are more of them than units
-    // (256), and it is the registers that part them only at 512 threads (a smaller
-    // tile's waves fit beside each other as they are).  Gradients of Ising layers:
-    // 8 x 20 qubits (2048 workgroups) 3.48 ms at WAVES 1 and 2.87 at 4, 1 x 22 (512)
-    // 2.03 and 1.67; 4 x 18 (128) 0.98 and 1.03, 64 x 12 (64) 0.42 and 0.43;
-    // complex128 4 x 20 (1024) 3.20 and 2.72, 4 x 18 (256) 0.92 and 1.02.
-    if constexpr (MaxThreads<R, RB>::value == 512)
-        if (nthreads == 512 && blocks > 256) {
-            hipLaunchKernelGGL((k_tile_rev<R, RB, 4>), dim3(unsigned(blocks)), dim3(nthreads), 0, st, jl, single);
-            return hipGetLastError();
-        }
-    hipLaunchKernelGGL((k_tile_rev<R, RB, 1>), dim3(unsigned(blocks)), dim3(nthreads), 0, st, jl, single);
+    hipLaunchKernelGGL((k_tile_rev<R, RB>), dim3(unsigned(blocks)), dim3(nthreads), 0, st, jl, single);
     return hipGetLastError();
 }
 

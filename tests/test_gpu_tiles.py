@@ -53,8 +53,7 @@ def test_tiles(oracle_mod, n, dt, mode, kinds, comb):
     assert len(params) == 0 or np.max(np.abs(g.cpu().numpy()[0] - ref["grad"])) <= tg * S
 
 
-# 256 and 258 reverse workgroups: the last launch at one workgroup a compute unit, the
-# first at two
+# every gate kind's reverse step, at 256 and 258 workgroups (one a compute unit, and more)
 @pytest.mark.parametrize("n,dt", [(14, "c64"), (13, "c128")])
 @pytest.mark.parametrize("batch", [128, 129])
 def test_reverse_occupancy(oracle_mod, n, dt, batch):

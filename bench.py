@@ -52,7 +52,7 @@ KERNEL_SOURCES = {
     "tile": ["common.h", "devutil.h", "gates.h", "kernels.h", "kern_tile.hip", "plan.cpp", "plan.h"],
     "fused": ["common.h", "devutil.h", "gates.h", "kernels.h", "kern_fused.hip", "plan.cpp", "plan.h"],
     "pauli": ["common.h", "devutil.h", "kernels.h", "kern_pauli.hip"],
-    "plain": ["common.h", "devutil.h", "gates.h", "kernels.h", "kern_plain.hip"],
+    "plain": ["common.h", "devutil.h", "finish.h", "gates.h", "kernels.h", "kern_plain.hip", "plaingate.h"],
 }
 TRAFFIC = {
     ("hea_n28_L12_tfim", "rev_tile"): (8.6047e+09, "34cae1f9856ca791"),

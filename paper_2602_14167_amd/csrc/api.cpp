@@ -97,7 +97,7 @@ bool small_n(int n) { return n >= 2 && n <= SM_QUBITS; }
 // the small-state kernel serves the calls whose state is too small for the
 // tiled plans (a wave's 64 lanes beside the register bits): complex64 to 10
 // qubits, complex128 to 9.  It replaces one launch per gate and sweep.  At 10
-// qubits in complex128 the tiled pass stays: it takes 113 us for one
+// qubits in complex128 the tiled pass stays: it takes about 100 us for one
 // parameter set and gains on larger batches.
 bool use_small(int mode, int n, int dtype) { return mode == TCNG_MODE_TILED && small_n(n) && !tiled_ok(n, dtype); }
 bool config_ok(const TileConfig& c, int dtype) {

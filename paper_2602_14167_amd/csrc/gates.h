@@ -367,11 +367,13 @@ __device__ __forceinline__ Regs<R, NB> app_diag_thread(Regs<R, NB> a, cx<R> f) {
     return a;
 }
 
-// Two-qubit diagonals with run-time bits: which amplitudes of the block a pair of
-// register bits selects is one uniform mask over the block, a thread bit is one
-// value per lane, and a sign is one XOR, so there is one copy of the code and no
-// choice per amplitude.  (Selecting each amplitude's entry from the diagonal took
-// 14 instructions an amplitude where the product takes 4.)
+// CZ with run-time bits: which amplitudes of the block a pair of register bits
+// selects is one uniform mask over the block, a thread bit is one value per lane, and
+// a sign is one XOR, so there is one copy of the code and no choice per amplitude.
+// RZZ takes its register bits at compile time, so its signs cost nothing.  (Selecting
+// each amplitude's entry from the diagonal took 14 instructions an amplitude where the
+// product takes 4: with listed tile addresses, 240 mixed gates on 24 qubits went from
+// 2.24 to 1.82 ms.)
 //
 // bit j of the result: bit r of j (r < 0: a thread bit, `none` instead)
 __device__ __forceinline__ uint32_t bits_of(int r, uint32_t none) {

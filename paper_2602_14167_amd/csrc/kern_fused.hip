@@ -58,7 +58,8 @@ struct TileIO {
 // (The pass lists the global offset and both layouts' addresses of every local
 // bit, zero beyond the tile, so the maps are sums under lane masks of values from
 // a few wide scalar loads.  With conditions on the bit and the tile size around
-// each, the loads came one at a time: some 150 dependent scalar loads per tile.)
+// each, the loads came one at a time, some 150 dependent scalar loads per tile: 256
+// snapshots of 20 qubits 2.89 -> 2.38 ms, 16 trajectories of 20 steps 5.43 -> 4.59.)
 template <int IT>
 __device__ __forceinline__ TileIO<IT> tile_io(cptr<FPass> P, int t, int nthr) {
     constexpr int IB = IT == 8 ? 3 : 2;   // iteration bits

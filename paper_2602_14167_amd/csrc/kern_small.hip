@@ -29,7 +29,7 @@ constexpr int SM_THREADS = 256;
 // circuit's own tables, so small circuits share a compute unit
 template <typename R>
 struct SmallLds {
-    size_t psi, lam, mat, ops, red, cot, groups, classes, terms, total;
+    size_t psi, lam, mat, ops, red, cot, esum, total;
     __host__ __device__ SmallLds(const SmallJob& J, int nwaves) {
         const size_t st = (size_t(1) << J.n) * sizeof(cx<R>);
         psi = 0;
@@ -38,10 +38,8 @@ struct SmallLds {
         ops = mat + size_t(J.tab_mat) * sizeof(cx<R>);
         red = ops + size_t(J.tab_ops) * sizeof(SOp);
         cot = red + size_t(J.tab_ops) * 2 * nwaves * sizeof(double);
-        groups = cot + (J.gate_grad ? size_t(2) * 32 * nwaves * sizeof(double) : 0);
-        classes = groups + size_t(J.tab_groups) * sizeof(PGroupFull);
-        terms = classes + size_t(J.tab_classes) * sizeof(PClassFull);
-        total = terms + size_t(J.tab_terms) * sizeof(PTermFull) + SM_THREADS / 64 * sizeof(double);
+        esum = cot + (J.gate_grad ? size_t(2) * 32 * nwaves * sizeof(double) : 0);
+        total = esum + SM_THREADS / 64 * sizeof(double);
     }
 };
 
@@ -103,6 +101,116 @@ __device__ __forceinline__ void quad_apply(int kind, const cx<R>* u, bool inv, b
     }
 }
 
+// H psi and this thread's part of <H>, for its A amplitudes t, t + T, ... (A = 1:
+// threads beyond a state smaller than a wave repeat others' work and drop it).
+// What bounds it is the latency of the tables' loads: they are the same for every
+// lane, so they are scalar loads, one serves A amplitudes, four one-term classes are
+// in flight at once, and the next group is loaded ahead.  (The classes and their
+// terms stand in group order, so the first term of a class is known before the
+// class is loaded.)  <H> of 300 / 1000 Z strings on 10 qubits, complex64: 39 / 124 us;
+// one flat load and wait a term for each amplitude took 235 / 801, the per-group
+// kernels' four workgroups 50 / 153.
+template <int A, typename R>
+__device__ __forceinline__ double pauli_part(const SmallJob& J, const cx<R>* psi, cx<R>* lam, cx<R>* glam, uint32_t t,
+                                             uint32_t T) {
+    cptr<PGroupFull> groups = as_const(J.groups);
+    cptr<PClassFull> classes = as_const(J.classes);
+    cptr<PTermFull> terms = as_const(J.terms);
+    const uint32_t dim = 1u << J.n;
+    uint32_t i[A];
+    cx<R> pj[A], acc[A];
+    double e[A];
+#pragma unroll
+    for (int a = 0; a < A; ++a) {
+        i[a] = (t + uint32_t(a) * T) & (dim - 1u);
+        pj[a] = psi[i[a]];
+        acc[a] = {R(0), R(0)};
+        e[a] = 0.0;
+    }
+    int m = 0;   // first term of class c
+    PGroupFull next{};
+    if (J.n_groups) next = groups[0];
+    for (int g = 0; g < J.n_groups; ++g) {
+        const PGroupFull G = next;
+        next = groups[g + 1 < J.n_groups ? g + 1 : g];
+        uint32_t j[A];
+        cx<R> pp[A];
+        double cre[A], cim[A];
+#pragma unroll
+        for (int a = 0; a < A; ++a) {
+            j[a] = i[a] ^ uint32_t(G.x);
+            pp[a] = psi[j[a]];
+            cre[a] = cim[a] = 0.0;
+        }
+        for (int c = G.class_begin; c < G.class_end;) {
+            if (c + 4 <= G.class_end) {   // (at least four terms from m on, then)
+                PClassFull K[4];
+                uint32_t z[4];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    K[k] = classes[c + k];
+                    z[k] = uint32_t(terms[m + k].z);
+                }
+                if (K[3].term_end == m + 4) {   // one term each: its sign is the class's factor
+#pragma unroll
+                    for (int k = 0; k < 4; ++k)
+#pragma unroll
+                        for (int a = 0; a < A; ++a) {
+                            const double s = (__popc(j[a] & z[k]) & 1) ? -1.0 : 1.0;
+                            cre[a] = fma(K[k].cre, s, cre[a]);
+                            cim[a] = fma(K[k].cim, s, cim[a]);
+                        }
+                    c += 4;
+                    m += 4;
+                    continue;
+                }
+            }
+            const PClassFull K = classes[c];
+            const int n_terms = K.term_end - m;
+            int odd[A];
+#pragma unroll
+            for (int a = 0; a < A; ++a) odd[a] = 0;
+            for (; m + 4 <= K.term_end; m += 4) {
+                uint32_t z[4];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) z[k] = uint32_t(terms[m + k].z);
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+#pragma unroll
+                    for (int a = 0; a < A; ++a) odd[a] += __popc(j[a] & z[k]) & 1;
+            }
+            for (; m < K.term_end; ++m) {
+                const uint32_t z = uint32_t(terms[m].z);
+#pragma unroll
+                for (int a = 0; a < A; ++a) odd[a] += __popc(j[a] & z) & 1;
+            }
+#pragma unroll
+            for (int a = 0; a < A; ++a) {
+                const double s = double(n_terms - 2 * odd[a]);
+                cre[a] = fma(K.cre, s, cre[a]);
+                cim[a] = fma(K.cim, s, cim[a]);
+            }
+            ++c;
+        }
+#pragma unroll
+        for (int a = 0; a < A; ++a) {
+            acc[a] = cfma(cx<R>{R(cre[a]), R(cim[a])}, pp[a], acc[a]);
+            const double rr = fma(double(pj[a].re), double(pp[a].re), double(pj[a].im) * double(pp[a].im));
+            const double ri = fma(double(pj[a].re), double(pp[a].im), -double(pj[a].im) * double(pp[a].re));
+            e[a] += cre[a] * rr - cim[a] * ri;
+        }
+    }
+    double sum = 0.0;
+    if (A == 1 && t >= dim) return sum;
+#pragma unroll
+    for (int a = 0; a < A; ++a) {
+        if (J.do_rev) lam[i[a]] = acc[a];
+        else if (glam) glam[i[a]] = acc[a];
+        sum += e[a];
+    }
+    return sum;
+}
+
 template <typename R>
 __global__ void __launch_bounds__(SM_THREADS) k_small(const SmallJob J) {
     extern __shared__ __align__(16) unsigned char smem[];
@@ -118,7 +226,7 @@ __global__ void __launch_bounds__(SM_THREADS) k_small(const SmallJob J) {
     SOp* ops = reinterpret_cast<SOp*>(smem + L.ops);
     double* red = reinterpret_cast<double*>(smem + L.red);
     double* cot = reinterpret_cast<double*>(smem + L.cot);
-    double* esum = reinterpret_cast<double*>(smem + L.total) - SM_THREADS / 64;
+    double* esum = reinterpret_cast<double*>(smem + L.esum);
     const int64_t b = blockIdx.x;
     cx<R>* gpsi = static_cast<cx<R>*>(J.psi) + b * J.stride;
     cx<R>* glam = J.lam ? static_cast<cx<R>*>(J.lam) + b * J.stride : nullptr;
@@ -127,22 +235,6 @@ __global__ void __launch_bounds__(SM_THREADS) k_small(const SmallJob J) {
     double* slots = J.slots ? J.slots + b * J.total_slots : nullptr;
 
     for (uint32_t i = t; i < dim; i += T) psi[i] = gpsi[i];
-    // the Pauli sum's tables, where they fit the launch's LDS
-    const PGroupFull* groups = J.groups;
-    const PClassFull* classes = J.classes;
-    const PTermFull* terms = J.terms;
-    if (J.tab_groups) {
-        PGroupFull* lg = reinterpret_cast<PGroupFull*>(smem + L.groups);
-        PClassFull* lc = reinterpret_cast<PClassFull*>(smem + L.classes);
-        PTermFull* lt = reinterpret_cast<PTermFull*>(smem + L.terms);
-        for (int i = t; i < J.tab_groups; i += T) lg[i] = groups[i];
-        for (int i = t; i < J.tab_classes; i += T) lc[i] = classes[i];
-        for (int i = t; i < J.tab_terms; i += T) lt[i] = terms[i];
-        groups = lg;
-        classes = lc;
-        terms = lt;
-    }
-
     // gates [begin, end) of chunk k and their matrices
     auto chunk = [&](int k) { return k ? J.chunks[k] : J.chunk0; };
     auto build = [&](const SChunk& C) {
@@ -195,31 +287,9 @@ __global__ void __launch_bounds__(SM_THREADS) k_small(const SmallJob J) {
     __syncthreads();
 
     if (J.do_pauli) {
-        double e = 0.0;
-        for (uint32_t i = t; i < dim; i += T) {
-            const cx<R> pj = psi[i];
-            cx<R> acc = {R(0), R(0)};
-            for (int g = 0; g < J.n_groups; ++g) {
-                const PGroupFull G = groups[g];
-                const uint32_t j = i ^ uint32_t(G.x);
-                const cx<R> pp = psi[j];
-                double cre = 0.0, cim = 0.0;
-                for (int c = G.class_begin; c < G.class_end; ++c) {
-                    const PClassFull K = classes[c];
-                    int odd = 0;
-                    for (int m = K.term_begin; m < K.term_end; ++m) odd += __popc(j & uint32_t(terms[m].z)) & 1;
-                    const double s = double(K.term_end - K.term_begin - 2 * odd);
-                    cre = fma(K.cre, s, cre);
-                    cim = fma(K.cim, s, cim);
-                }
-                acc = cfma(cx<R>{R(cre), R(cim)}, pp, acc);
-                const double rr = fma(double(pj.re), double(pp.re), double(pj.im) * double(pp.im));
-                const double ri = fma(double(pj.re), double(pp.im), -double(pj.im) * double(pp.re));
-                e += cre * rr - cim * ri;
-            }
-            if (J.do_rev) lam[i] = acc;
-            else if (glam) glam[i] = acc;
-        }
+        double e = dim >= 4u * T   ? pauli_part<4>(J, psi, lam, glam, t, T)
+                   : dim >= 2u * T ? pauli_part<2>(J, psi, lam, glam, t, T)
+                                   : pauli_part<1>(J, psi, lam, glam, t, T);
         e = wave_sum(e);
         if (lane == 0) esum[wave] = e;
         __syncthreads();
@@ -369,11 +439,9 @@ template <typename R>
 hipError_t launch_small(const SmallJob& job, int64_t batch, hipStream_t st) {
     if (batch <= 0) return hipSuccess;
     if (job.n < 2 || job.n > SM_QUBITS || job.tab_ops > SM_OPS || job.tab_mat > SM_MAT) return hipErrorInvalidValue;
-    SmallJob J = job;
-    if (J.tab_groups > SM_TERMS || J.tab_classes > SM_TERMS || J.tab_terms > SM_TERMS)
-        J.tab_groups = J.tab_classes = J.tab_terms = 0;   // read in place
-    const int nt = std::max(64, std::min(SM_THREADS, 1 << (J.n - 1)));
-    hipLaunchKernelGGL((k_small<R>), dim3(unsigned(batch)), dim3(unsigned(nt)), SmallLds<R>(J, nt / 64).total, st, J);
+    const int nt = std::max(64, std::min(SM_THREADS, 1 << (job.n - 1)));
+    hipLaunchKernelGGL((k_small<R>), dim3(unsigned(batch)), dim3(unsigned(nt)), SmallLds<R>(job, nt / 64).total, st,
+                       job);
     return hipGetLastError();
 }
 template hipError_t launch_small<float>(const SmallJob&, int64_t, hipStream_t);

@@ -282,8 +282,7 @@ struct SmallJob {
     double* gate_grad;         // [batch][n_gates][15] or null
     int64_t stride;
     int32_t n, n_chunks, n_params, n_gates, total_slots, n_groups;
-    int32_t tab_ops, tab_mat;                          // LDS tables: the most of any chunk,
-    int32_t tab_groups, tab_classes, tab_terms;        // and the Pauli sum's (0: read in place)
+    int32_t tab_ops, tab_mat;  // LDS tables: the most of any chunk
     int32_t do_fwd, do_pauli, do_rev;
 };
 template <typename R>

@@ -34,7 +34,7 @@ struct SmallLds {
         const size_t st = (size_t(1) << J.n) * sizeof(cx<R>);
         psi = 0;
         lam = psi + st;
-        mat = lam + st;
+        mat = lam + (J.do_rev ? st : 0);
         ops = mat + size_t(J.tab_mat) * sizeof(cx<R>);
         red = ops + size_t(J.tab_ops) * sizeof(SOp);
         cot = red + size_t(J.tab_ops) * 2 * nwaves * sizeof(double);
@@ -44,6 +44,22 @@ struct SmallLds {
 };
 
 __device__ __forceinline__ uint32_t insert_zero(uint32_t v, int q) { return ((v >> q) << (q + 1)) | (v & ((1u << q) - 1u)); }
+
+// a state between global memory and LDS, 16 bytes an access (the state descriptor's
+// alignment; four amplitudes or more), two in flight
+template <typename R>
+__device__ __forceinline__ void copy_state(cx<R>* dst, const cx<R>* src, uint32_t dim, uint32_t t, uint32_t T) {
+    typedef float vec16 __attribute__((vector_size(16), may_alias));
+    vec16* d = reinterpret_cast<vec16*>(dst);
+    const vec16* s = reinterpret_cast<const vec16*>(src);
+    const uint32_t chunks = dim * uint32_t(sizeof(cx<R>)) / 16;
+    for (uint32_t c = t; c < chunks; c += 2 * T) {
+        const bool more = c + T < chunks;
+        const vec16 a = s[c], b = s[more ? c + T : c];
+        d[c] = a;
+        if (more) d[c + T] = b;
+    }
+}
 
 // order of the LDS operations between gates: a barrier, or nothing but program
 // order while one wave does all of them
@@ -110,7 +126,7 @@ __device__ __forceinline__ void quad_apply(int kind, const cx<R>* u, bool inv, b
 // class is loaded.)  <H> of 300 / 1000 Z strings on 10 qubits, complex64: 39 / 124 us;
 // one flat load and wait a term for each amplitude took 235 / 801, the per-group
 // kernels' four workgroups 50 / 153.
-template <int A, typename R>
+template <bool REV, int A, typename R>
 __device__ __forceinline__ double pauli_part(const SmallJob& J, const cx<R>* psi, cx<R>* lam, cx<R>* glam, uint32_t t,
                                              uint32_t T) {
     cptr<PGroupFull> groups = as_const(J.groups);
@@ -204,15 +220,23 @@ __device__ __forceinline__ double pauli_part(const SmallJob& J, const cx<R>* psi
     if (A == 1 && t >= dim) return sum;
 #pragma unroll
     for (int a = 0; a < A; ++a) {
-        if (J.do_rev) lam[i[a]] = acc[a];
+        if (REV && J.do_rev) lam[i[a]] = acc[a];
         else if (glam) glam[i[a]] = acc[a];
         sum += e[a];
     }
     return sum;
 }
 
-template <typename R>
-__global__ void __launch_bounds__(SM_THREADS) k_small(const SmallJob J) {
+// PARTS: what a launch may have to do: Pauli sums only, gates too, or also the
+// derivatives of constant two-qubit matrices.  The 32 float64 sums of those take 213
+// registers in complex64 and 290 in complex128; without them gates take 106 and 165, and
+// Pauli sums alone 93 and 62.  Large batches need the waves that this leaves room for:
+// <H> of 4 Z strings on 32768 states of 9 qubits in complex128 took 489 us in one
+// kernel for all, where the per-group kernels take 64; now 45.
+enum SmallParts { SM_PAULI, SM_GATES, SM_COTANGENTS };
+
+template <typename R, int PARTS>
+__global__ void __launch_bounds__(SM_THREADS, PARTS == SM_PAULI ? 5 : 1) k_small(const SmallJob J) {
     extern __shared__ __align__(16) unsigned char smem[];
     const int n = J.n, T = blockDim.x, t = threadIdx.x;
     const int nwaves = T >> 6;
@@ -234,7 +258,7 @@ __global__ void __launch_bounds__(SM_THREADS) k_small(const SmallJob J) {
     const cx<R>* cm = static_cast<const cx<R>*>(J.cm);
     double* slots = J.slots ? J.slots + b * J.total_slots : nullptr;
 
-    for (uint32_t i = t; i < dim; i += T) psi[i] = gpsi[i];
+    copy_state(psi, gpsi, dim, t, T);
     // gates [begin, end) of chunk k and their matrices
     auto chunk = [&](int k) { return k ? J.chunks[k] : J.chunk0; };
     auto build = [&](const SChunk& C) {
@@ -247,7 +271,7 @@ __global__ void __launch_bounds__(SM_THREADS) k_small(const SmallJob J) {
         __syncthreads();
     };
 
-    if (J.do_fwd)
+    if (PARTS >= SM_GATES && J.do_fwd)
         for (int k = 0; k < J.n_chunks; ++k) {
             const SChunk C = chunk(k);
             if (k) __syncthreads();   // the previous chunk's tables
@@ -287,9 +311,11 @@ __global__ void __launch_bounds__(SM_THREADS) k_small(const SmallJob J) {
     __syncthreads();
 
     if (J.do_pauli) {
-        double e = dim >= 4u * T   ? pauli_part<4>(J, psi, lam, glam, t, T)
-                   : dim >= 2u * T ? pauli_part<2>(J, psi, lam, glam, t, T)
-                                   : pauli_part<1>(J, psi, lam, glam, t, T);
+        constexpr bool REV = PARTS >= SM_GATES;
+        double e;
+        if (sizeof(R) == 4 && dim == 4u * T) e = pauli_part<REV, sizeof(R) == 4 ? 4 : 1>(J, psi, lam, glam, t, T);
+        else if (dim == 2u * T) e = pauli_part<REV, 2>(J, psi, lam, glam, t, T);
+        else e = pauli_part<REV, 1>(J, psi, lam, glam, t, T);
         e = wave_sum(e);
         if (lane == 0) esum[wave] = e;
         __syncthreads();
@@ -300,7 +326,7 @@ __global__ void __launch_bounds__(SM_THREADS) k_small(const SmallJob J) {
         }
     }
 
-    if (J.do_rev) {
+    if (PARTS >= SM_GATES && J.do_rev) {
         for (int k = J.n_chunks - 1; k >= 0; --k) {
             const SChunk C = chunk(k);
             if (J.n_chunks > 1) build(C);   // (one chunk: the forward sweep's tables stand)
@@ -334,7 +360,7 @@ __global__ void __launch_bounds__(SM_THREADS) k_small(const SmallJob J) {
                 } else {
                     const uint32_t b0 = 1u << q0, b1 = 1u << q1;
                     const int lo = q0 < q1 ? q0 : q1, hi = q0 < q1 ? q1 : q0;
-                    const bool want_cot = kind == K_U2 && slot >= 0 && J.gate_grad;
+                    const bool want_cot = PARTS == SM_COTANGENTS && kind == K_U2 && slot >= 0;
                     double G[32];
                     if (want_cot)
 #pragma unroll
@@ -412,10 +438,9 @@ __global__ void __launch_bounds__(SM_THREADS) k_small(const SmallJob J) {
         }
     }
 
-    if (J.do_fwd)
-        for (uint32_t i = t; i < dim; i += T) gpsi[i] = psi[i];
-    if (J.do_rev) {
-        for (uint32_t i = t; i < dim; i += T) glam[i] = lam[i];
+    if (PARTS >= SM_GATES && J.do_fwd) copy_state(gpsi, psi, dim, t, T);
+    if (PARTS >= SM_GATES && J.do_rev) {
+        copy_state(glam, lam, dim, t, T);
         FinishJob F{};
         F.slots = slots;
         F.slot_ptr = J.slot_ptr;
@@ -438,10 +463,10 @@ __global__ void __launch_bounds__(SM_THREADS) k_small(const SmallJob J) {
 template <typename R>
 hipError_t launch_small(const SmallJob& job, int64_t batch, hipStream_t st) {
     if (batch <= 0) return hipSuccess;
-    if (job.n < 2 || job.n > SM_QUBITS || job.tab_ops > SM_OPS || job.tab_mat > SM_MAT) return hipErrorInvalidValue;
+    if (job.n < 2 || job.n > (sizeof(R) == 4 ? SM_QUBITS : SM_QUBITS - 1) || job.tab_ops > SM_OPS || job.tab_mat > SM_MAT) return hipErrorInvalidValue;
     const int nt = std::max(64, std::min(SM_THREADS, 1 << (job.n - 1)));
-    hipLaunchKernelGGL((k_small<R>), dim3(unsigned(batch)), dim3(unsigned(nt)), SmallLds<R>(job, nt / 64).total, st,
-                       job);
+    auto kernel = job.gate_grad ? k_small<R, SM_COTANGENTS> : job.do_fwd ? k_small<R, SM_GATES> : k_small<R, SM_PAULI>;
+    hipLaunchKernelGGL(kernel, dim3(unsigned(batch)), dim3(unsigned(nt)), SmallLds<R>(job, nt / 64).total, st, job);
     return hipGetLastError();
 }
 template hipError_t launch_small<float>(const SmallJob&, int64_t, hipStream_t);

@@ -68,15 +68,17 @@ def test_many_terms(oracle_mod, n, terms, kind, dt):
 
 
 # the small-state kernel serves every sum at these sizes, so it may not be slower than the
-# per-group kernels it replaces; a quarter for timing noise (one flat load and
-# wait per term made it 2.4 to 4.7 times slower here)
-@pytest.mark.parametrize("n,dt,terms,kind", [(10, "c64", 300, "diag"), (10, "c64", 1000, "few"), (8, "c64", 1000, "diag"),
-                                             (9, "c128", 1000, "diag")])
-def test_not_slower_than_per_group(n, dt, terms, kind):
+# per-group kernels it replaces; a quarter for timing noise.  (One flat load and wait
+# per term made single states 2.4 to 4.7 times slower here, and one kernel for all
+# uses, with one wave a SIMD, the large batch 7.6 times.)
+@pytest.mark.parametrize("n,dt,terms,kind,batch", [
+    (10, "c64", 300, "diag", 1), (10, "c64", 1000, "few", 1), (8, "c64", 1000, "diag", 1), (9, "c128", 1000, "diag", 1),
+    (9, "c128", 4, "diag", 32768), (9, "c128", 20, "few", 32768), (10, "c64", 4, "diag", 32768)])
+def test_not_slower_than_per_group(n, dt, terms, kind, batch):
     import paper_2602_14167_amd as P
     r = np.random.default_rng(terms)
     H = P.PauliSum(n, *pauli_sum(n, terms, kind, r))
-    psi = states(n, 1, dt, r)
+    psi = states(n, 1, dt, r).repeat(batch, 1)
     assert best(lambda: P.expect_pauli(psi, H)) <= 1.25 * best(lambda: P.expect_pauli(psi, H, mode="plain"))
 
 

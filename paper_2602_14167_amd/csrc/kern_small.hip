@@ -26,22 +26,30 @@ namespace {
 constexpr int SM_THREADS = 256;
 
 // LDS layout of a workgroup (bytes): the host sizes the launch with it, by the
-// circuit's own tables, so small circuits share a compute unit
+// circuit's own tables, so small circuits share a compute unit.  The largest launch
+// (every table full) has to stay within the 64 KiB that a launch may ask for without
+// a function attribute.
 template <typename R>
 struct SmallLds {
     size_t psi, lam, mat, ops, red, cot, esum, total;
-    __host__ __device__ SmallLds(const SmallJob& J, int nwaves) {
-        const size_t st = (size_t(1) << J.n) * sizeof(cx<R>);
-        psi = 0;
-        lam = psi + st;
-        mat = lam + (J.do_rev ? st : 0);
-        ops = mat + size_t(J.tab_mat) * sizeof(cx<R>);
-        red = ops + size_t(J.tab_ops) * sizeof(SOp);
-        cot = red + size_t(J.tab_ops) * 2 * nwaves * sizeof(double);
-        esum = cot + (J.gate_grad ? size_t(2) * 32 * nwaves * sizeof(double) : 0);
-        total = esum + SM_THREADS / 64 * sizeof(double);
-    }
+    __host__ __device__ constexpr SmallLds(int n, int tab_mat, int tab_ops, bool rev, bool cotangents, int nwaves)
+        : psi(0),
+          lam((size_t(1) << n) * sizeof(cx<R>)),
+          mat(lam + (rev ? lam : 0)),
+          ops(mat + size_t(tab_mat) * sizeof(cx<R>)),
+          red(ops + size_t(tab_ops) * sizeof(SOp)),
+          cot(red + size_t(tab_ops) * 2 * nwaves * sizeof(double)),
+          esum(cot + (cotangents ? size_t(2) * 32 * nwaves * sizeof(double) : 0)),
+          total(esum + SM_THREADS / 64 * sizeof(double)) {}
+    __host__ __device__ SmallLds(const SmallJob& J, int nwaves)
+        : SmallLds(J.n, J.tab_mat, J.tab_ops, J.do_rev != 0, J.gate_grad != nullptr, nwaves) {}
 };
+// qubits of the largest state
+template <typename R>
+constexpr int small_qubits() { return sizeof(R) == 4 ? SM_QUBITS : SM_QUBITS - 1; }
+static_assert(SmallLds<float>(small_qubits<float>(), SM_MAT, SM_OPS, true, true, SM_THREADS / 64).total <= 65536 &&
+                  SmallLds<double>(small_qubits<double>(), SM_MAT, SM_OPS, true, true, SM_THREADS / 64).total <= 65536,
+              "LDS of the largest launch");
 
 __device__ __forceinline__ uint32_t insert_zero(uint32_t v, int q) { return ((v >> q) << (q + 1)) | (v & ((1u << q) - 1u)); }
 
@@ -463,7 +471,7 @@ __global__ void __launch_bounds__(SM_THREADS, PARTS == SM_PAULI ? 5 : 1) k_small
 template <typename R>
 hipError_t launch_small(const SmallJob& job, int64_t batch, hipStream_t st) {
     if (batch <= 0) return hipSuccess;
-    if (job.n < 2 || job.n > (sizeof(R) == 4 ? SM_QUBITS : SM_QUBITS - 1) || job.tab_ops > SM_OPS || job.tab_mat > SM_MAT) return hipErrorInvalidValue;
+    if (job.n < 2 || job.n > small_qubits<R>() || job.tab_ops > SM_OPS || job.tab_mat > SM_MAT) return hipErrorInvalidValue;
     const int nt = std::max(64, std::min(SM_THREADS, 1 << (job.n - 1)));
     auto kernel = job.gate_grad ? k_small<R, SM_COTANGENTS> : job.do_fwd ? k_small<R, SM_GATES> : k_small<R, SM_PAULI>;
     hipLaunchKernelGGL(kernel, dim3(unsigned(batch)), dim3(unsigned(nt)), SmallLds<R>(job, nt / 64).total, st, job);

@@ -67,6 +67,28 @@ def test_many_terms(oracle_mod, n, terms, kind, dt):
         assert abs(E[b] - np.vdot(w, ref).real) <= TOL[dt] * S
 
 
+# the largest workgroup: full tables of gates (192 one-qubit gates in one chunk) and of
+# matrices (64 two-qubit gates in the next), gate gradients, more than 256 X-masks
+@pytest.mark.parametrize("n,dt", [(10, "c64"), (9, "c128")])
+def test_full_tables(oracle_mod, n, dt):
+    import paper_2602_14167_amd as P
+    r = np.random.default_rng(n)
+    one, params, _ = W.random_circuit(n, 192, r, kinds=[W.RX, W.RY, W.RZ])
+    two, _, mats = W.random_circuit(n, 64, r, kinds=[W.U2])
+    gates = np.concatenate([one, two])
+    codes, coeffs = pauli_sum(n, 300, "rand", r)
+    H = P.PauliSum(n, codes, coeffs)
+    real = torch.float32 if dt == "c64" else torch.float64
+    E, g, gg = P.expect_grad(P.Circuit(n, gates, len(params), mats), torch.as_tensor(params).to("cuda", real), H,
+                             dtype=TDT[dt], want_gate_grad=True)
+    ref = oracle_mod.expect_grad(n, gates, W.round_params(params, dt), codes, coeffs, W.round_mats(mats, dt), want_lie=True)
+    S = float(np.abs(coeffs).sum())
+    tg = 1e-4 if dt == "c64" else 1e-12
+    assert abs(E.item() - ref["E"]) <= TOL[dt] * S
+    assert np.max(np.abs(g.cpu().numpy()[0] - ref["grad"])) <= tg * S
+    assert np.max(np.abs(gg.cpu().numpy()[0][192:] - ref["lie"][192:])) <= tg * S
+
+
 # the small-state kernel serves every sum at these sizes, so it may not be slower than the
 # per-group kernels it replaces; a quarter for timing noise.  (One flat load and wait
 # per term made single states 2.4 to 4.7 times slower here, and one kernel for all

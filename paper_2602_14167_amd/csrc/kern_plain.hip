@@ -357,25 +357,26 @@ struct RowTable {
     int len;
 };
 __global__ void __launch_bounds__(256) k_rowsum(const RowTable a, const RowTable b) {
-    int64_t row = int64_t(blockIdx.x) * 4 + (threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
-    if (row >= a.rows + b.rows) return;   // whole wave leaves together
-    const bool second = row >= a.rows;
-    if (second) row -= a.rows;
-    const int len = second ? b.len : a.len;
-    const double* p = (second ? b.in : a.in) + size_t(row) * len;
-    double v = 0.0;
-    int i = lane;
-    for (; i + 7 * 64 < len; i += 8 * 64) {
-        double x[8];
+    // (whole waves leave together)
+    for (int64_t r = int64_t(blockIdx.x) * 4 + (threadIdx.x >> 6); r < a.rows + b.rows; r += int64_t(gridDim.x) * 4) {
+        const bool second = r >= a.rows;
+        const int64_t row = second ? r - a.rows : r;
+        const int len = second ? b.len : a.len;
+        const double* p = (second ? b.in : a.in) + size_t(row) * len;
+        double v = 0.0;
+        int i = lane;
+        for (; i + 7 * 64 < len; i += 8 * 64) {
+            double x[8];
 #pragma unroll
-        for (int k = 0; k < 8; ++k) x[k] = p[i + 64 * k];
+            for (int k = 0; k < 8; ++k) x[k] = p[i + 64 * k];
 #pragma unroll
-        for (int k = 0; k < 8; ++k) v += x[k];
+            for (int k = 0; k < 8; ++k) v += x[k];
+        }
+        for (; i < len; i += 64) v += p[i];
+        v = wave_sum(v);
+        if (lane == 0) (second ? b.out : a.out)[row] = v;
     }
-    for (; i < len; i += 64) v += p[i];
-    v = wave_sum(v);
-    if (lane == 0) (second ? b.out : a.out)[row] = v;
 }
 
 __global__ void k_finish(const double* __restrict__ slots, int total_slots, const int32_t* __restrict__ slot_ptr,
@@ -384,37 +385,38 @@ __global__ void k_finish(const double* __restrict__ slots, int total_slots, cons
                          double* __restrict__ gate_grad, const int32_t* __restrict__ gate_slot,
                          const double* __restrict__ u2m, const int32_t* __restrict__ gate_mat, int n_gates) {
     const int64_t per = int64_t(1) + n_params + (gate_grad ? GATE_OUTS * int64_t(n_gates) : 0);
-    const int64_t tid = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (tid >= per * batch) return;
-    const int64_t b = tid / per;
-    FinishJob F{};
-    F.slots = slots + size_t(b) * total_slots;
-    F.erow = erow + size_t(b) * erows;
-    F.slot_ptr = slot_ptr;
-    F.slot_idx = slot_idx;
-    F.gate_slot = gate_slot;
-    F.u2m = u2m;
-    F.gate_mat = gate_mat;
-    F.energy = energy + b;
-    F.grad = grad ? grad + size_t(b) * n_params : nullptr;
-    F.gate_grad = gate_grad ? gate_grad + size_t(b) * n_gates * 15 : nullptr;
-    F.n_params = n_params;
-    F.n_gates = n_gates;
-    F.erows = erows;
-    finish_one(F, tid - b * per);
+    for (int64_t tid = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; tid < per * batch;
+         tid += int64_t(gridDim.x) * blockDim.x) {
+        const int64_t b = tid / per;
+        FinishJob F{};
+        F.slots = slots + size_t(b) * total_slots;
+        F.erow = erow + size_t(b) * erows;
+        F.slot_ptr = slot_ptr;
+        F.slot_idx = slot_idx;
+        F.gate_slot = gate_slot;
+        F.u2m = u2m;
+        F.gate_mat = gate_mat;
+        F.energy = energy + b;
+        F.grad = grad ? grad + size_t(b) * n_params : nullptr;
+        F.gate_grad = gate_grad ? gate_grad + size_t(b) * n_gates * 15 : nullptr;
+        F.n_params = n_params;
+        F.n_gates = n_gates;
+        F.erows = erows;
+        finish_one(F, tid - b * per);
+    }
 }
 
 __global__ void k_finish_multi(const FinishJob* __restrict__ jobs, const int64_t* __restrict__ prefix, int njobs,
                                int64_t total) {
-    const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (i >= total) return;
-    int lo = 0, hi = njobs - 1;
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (prefix[mid] <= i) lo = mid;
-        else hi = mid - 1;
+    for (int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; i < total; i += int64_t(gridDim.x) * blockDim.x) {
+        int lo = 0, hi = njobs - 1;
+        while (lo < hi) {
+            const int mid = (lo + hi + 1) >> 1;
+            if (prefix[mid] <= i) lo = mid;
+            else hi = mid - 1;
+        }
+        finish_one(jobs[lo], i - prefix[lo]);
     }
-    finish_one(jobs[lo], i - prefix[lo]);
 }
 
 // ---------------------------------------------------------------------------
@@ -805,7 +807,7 @@ hipError_t launch_zero(double* p, size_t count, hipStream_t st) {
 static hipError_t launch_rowsum(const RowTable& a, const RowTable& b, hipStream_t st) {
     const int64_t rows = a.rows + b.rows;
     if (rows <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_rowsum, dim3(unsigned((rows + 3) / 4)), dim3(256), 0, st, a, b);
+    hipLaunchKernelGGL(k_rowsum, dim3(grid_blocks((rows + 3) / 4)), dim3(256), 0, st, a, b);
     return hipGetLastError();
 }
 
@@ -822,7 +824,7 @@ hipError_t launch_finish(const double* part, int total_slots, int wgs, const int
     if (e != hipSuccess) return e;
     const int64_t per = 1 + n_params + (gate_grad ? GATE_OUTS * int64_t(n_gates) : 0);
     const int64_t work = per * batch;
-    hipLaunchKernelGGL(k_finish, dim3(unsigned((work + 255) / 256)), dim3(256), 0, st, slots, total_slots, slot_ptr,
+    hipLaunchKernelGGL(k_finish, dim3(grid_blocks((work + 255) / 256)), dim3(256), 0, st, slots, total_slots, slot_ptr,
                        slot_idx, n_params, erow, erows, batch, energy, grad, gate_grad, gate_slot, u2_mats_c128,
                        gate_mat, n_gates);
     return hipGetLastError();
@@ -834,7 +836,7 @@ hipError_t launch_finish_multi(const double* part, int64_t prows, int wgs, const
     hipError_t e = launch_rowsum({part, slot_sums, prows, wgs}, {epart, erow_sums, erows_total, ewgs}, st);
     if (e != hipSuccess) return e;
     if (total <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_finish_multi, dim3(unsigned((total + 255) / 256)), dim3(256), 0, st, jobs, prefix, njobs,
+    hipLaunchKernelGGL(k_finish_multi, dim3(grid_blocks((total + 255) / 256)), dim3(256), 0, st, jobs, prefix, njobs,
                        total);
     return hipGetLastError();
 }

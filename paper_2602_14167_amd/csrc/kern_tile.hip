@@ -1246,14 +1246,9 @@ __global__ void __launch_bounds__(1 << (q_tile_bits<R>() - QR)) k_rounds_rev(con
 // its matrix entries), not one per phase and gate.  Latency-bound: one thread
 // per step took 24 us at 10 qubits and 36 us at 21 (complex128).
 template <typename R>
-__global__ void k_rounds_coef(const QStep* __restrict__ fsteps, int nf, const QStep* __restrict__ rsteps, int nr,
-                              const cx<R>* __restrict__ opm, int n_gates, int64_t batch, QCoef<R>* __restrict__ out) {
-    constexpr int NJ = 1 << QREG;
-    const int64_t tid = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    const int64_t i = tid / NJ;
-    const int j = int(tid % NJ);
-    const int per = nf + nr;
-    if (i >= int64_t(per) * batch) return;
+__device__ __forceinline__ void coef_entry(const QStep* __restrict__ fsteps, int nf, const QStep* __restrict__ rsteps,
+                                           int per, const cx<R>* __restrict__ opm, int n_gates, int64_t i, int j,
+                                           QCoef<R>* __restrict__ out) {
     const int64_t b = i / per;
     const int s = int(i - b * per);
     const QStep S = s < nf ? fsteps[s] : rsteps[s - nf];
@@ -1306,6 +1301,14 @@ __global__ void k_rounds_coef(const QStep* __restrict__ fsteps, int nf, const QS
     c[QPH + 2 * j] = ph.re;
     c[QPH + 2 * j + 1] = ph.im;
 }
+template <typename R>
+__global__ void k_rounds_coef(const QStep* __restrict__ fsteps, int nf, const QStep* __restrict__ rsteps, int nr,
+                              const cx<R>* __restrict__ opm, int n_gates, int64_t batch, QCoef<R>* __restrict__ out) {
+    constexpr int NJ = 1 << QREG;
+    const int64_t work = int64_t(nf + nr) * batch * NJ;
+    for (int64_t tid = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; tid < work; tid += int64_t(gridDim.x) * blockDim.x)
+        coef_entry<R>(fsteps, nf, rsteps, nf + nr, opm, n_gates, tid / NJ, int(tid % NJ), out);
+}
 
 }  // namespace
 
@@ -1340,7 +1343,7 @@ hipError_t launch_rounds_coef(const QStep* fsteps, int nf, const QStep* rsteps, 
                               int64_t batch, void* out, hipStream_t st) {
     const int64_t work = int64_t(nf + nr) * batch * (1 << QREG);   // a thread per block and register amplitude
     if (work == 0) return hipSuccess;
-    hipLaunchKernelGGL((k_rounds_coef<R>), dim3(unsigned((work + 255) / 256)), dim3(256), 0, st, fsteps, nf, rsteps,
+    hipLaunchKernelGGL((k_rounds_coef<R>), dim3(grid_blocks((work + 255) / 256)), dim3(256), 0, st, fsteps, nf, rsteps,
                        nr, static_cast<const cx<R>*>(opm), n_gates, batch, static_cast<QCoef<R>*>(out));
     return hipGetLastError();
 }

@@ -5,6 +5,13 @@
 
 namespace tcng {
 
+// blocks of a launch of 256 threads each whose kernel loops over the rest: a grid may
+// not hold 2^32 threads
+inline unsigned grid_blocks(int64_t blocks) {
+    constexpr int64_t most = 0xFFFFFFFFll / 256;
+    return unsigned(blocks < most ? blocks : most);
+}
+
 // device copies of a circuit plan
 struct DevPlan {
     const Pass* passes = nullptr;

@@ -853,9 +853,8 @@ __device__ __forceinline__ void fused_osum_one(const double* __restrict__ opart,
 // os: doubles of one outer product (512 for 16 x 16 blocks, 2048 for 32 x 32)
 __global__ void k_fused_osum(const double* __restrict__ opart, int64_t rows, int wgs, double* __restrict__ osum,
                              int os) {
-    const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (i >= rows * os) return;
-    fused_osum_one(opart, wgs, osum, i, os);
+    for (int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; i < rows * os; i += int64_t(gridDim.x) * blockDim.x)
+        fused_osum_one(opart, wgs, osum, i, os);
 }
 
 // uneven batch: circuit blockIdx.y, entries of its n_blocks outer products
@@ -1102,7 +1101,7 @@ hipError_t launch_fused_grad(const FPhase* phases, const Op* ops, int n_blocks, 
     if (n_blocks == 0 || batch == 0) return hipSuccess;
     const int64_t rows = batch * int64_t(n_blocks);
     const int os = kb == 5 ? 4 * OSTRIDE : OSTRIDE;
-    hipLaunchKernelGGL(k_fused_osum, dim3(unsigned((rows * os + 255) / 256)), dim3(256), 0, st, opart, rows, wgs,
+    hipLaunchKernelGGL(k_fused_osum, dim3(grid_blocks((rows * os + 255) / 256)), dim3(256), 0, st, opart, rows, wgs,
                        osum, os);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;

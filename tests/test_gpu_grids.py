@@ -19,7 +19,7 @@ BATCH = 65535
 
 @pytest.fixture(autouse=True)
 def room():
-    torch.cuda.empty_cache()   # (up to 60 GB at a time)
+    torch.cuda.empty_cache()   # (up to 150 GB at a time)
     yield
     torch.cuda.empty_cache()
 
@@ -70,3 +70,27 @@ def test_final_sums_beyond_a_grid():
     E, _, gg = P.expect_grad(circ, None, H, batch=BATCH, mode="plain", want_gate_grad=True)
     assert torch.equal(E, torch.ones_like(E))
     assert gg.abs().amax().item() == 0.0
+
+
+def test_block_sums_beyond_a_grid():
+    # 65535 x 129 or more matrix-core blocks x 512 sums
+    import paper_2602_14167_amd as P
+    r = np.random.default_rng(9)
+    rows = []
+    while len(rows) < 2000:
+        a, b = r.permutation(9)[:2]
+        rows += [W.gate(W.RY, a, p0=int(r.integers(4))), W.gate(W.CNOT, a, b)]
+        if len(rows) % 40 == 0 and P.fused_plan_inspect(9, W.as_gate_array(rows), 4)[4] >= 130:
+            break
+    gates = W.as_gate_array(rows)
+    blocks = P.fused_plan_inspect(9, gates, 4)[4]
+    assert 130 <= blocks <= 140
+    circ = P.Circuit(9, gates, 4)
+    codes, coeffs = W.random_pauli_sum(9, 6, r)
+    H = P.PauliSum(9, codes, coeffs)
+    t = torch.as_tensor(r.uniform(-np.pi, np.pi, 4), dtype=torch.float32, device="cuda")
+    E1, g1 = P.expect_grad(circ, t, H, mode="fused")
+    E, g = P.expect_grad(circ, t.repeat(BATCH, 1), H, mode="fused")
+    assert torch.equal(E[:1].expand(BATCH), E) and torch.equal(g1.expand(BATCH, -1), g)
+    # (one member's energy is summed by two workgroups, a member's of the batch by one)
+    assert abs(E[0].item() - E1.item()) <= 2.0 ** -40 * np.abs(coeffs).sum()

@@ -80,8 +80,8 @@ __device__ __forceinline__ void gate1_unit(cx<float>* psi, uint64_t w, int q, co
         cx<float> a0, a1, a2, a3;
         ld2(psi + 4 * w, a0, a1);
         ld2(psi + 4 * w + 2, a2, a3);
-        mv2(u, a0, a1);
-        mv2(u, a2, a3);
+        mv2<false>(u, a0, a1);
+        mv2<false>(u, a2, a3);
         st2(psi + 4 * w, a0, a1);
         st2(psi + 4 * w + 2, a2, a3);
     } else {
@@ -89,8 +89,8 @@ __device__ __forceinline__ void gate1_unit(cx<float>* psi, uint64_t w, int q, co
         cx<float> a0, a1, c0, c1;
         ld2(psi + i0, a0, a1);
         ld2(psi + i0 + (uint64_t(1) << q), c0, c1);
-        mv2(u, a0, c0);
-        mv2(u, a1, c1);
+        mv2<false>(u, a0, c0);
+        mv2<false>(u, a1, c1);
         st2(psi + i0, a0, a1);
         st2(psi + i0 + (uint64_t(1) << q), c0, c1);
     }
@@ -98,7 +98,7 @@ __device__ __forceinline__ void gate1_unit(cx<float>* psi, uint64_t w, int q, co
 __device__ __forceinline__ void gate1_unit(cx<double>* psi, uint64_t w, int q, const cx<double>* u) {
     const uint64_t i0 = insert0(w, q), i1 = i0 | (uint64_t(1) << q);
     cx<double> a0 = ld1(psi + i0), a1 = ld1(psi + i1);
-    mv2(u, a0, a1);
+    mv2<false>(u, a0, a1);
     st1(psi + i0, a0);
     st1(psi + i1, a1);
 }
@@ -135,7 +135,7 @@ __global__ void k_gate1_tiny(cx<R>* __restrict__ state, int64_t stride, int q, i
     gate_mat1<R>(kind, params ? params + b * pstride : nullptr, p0, cm, mat, umat, inv != 0, u);
     (void)q;
     cx<R> a0 = psi[0], a1 = psi[1];
-    mv2(u, a0, a1);
+    mv2<false>(u, a0, a1);
     psi[0] = a0;
     psi[1] = a1;
 }
@@ -177,8 +177,8 @@ k_gate2(cx<R>* __restrict__ state, int64_t stride, int n, int q0, int q1, int ki
                 ld2(psi + (i | m1), x[1], y[1]);
                 ld2(psi + (i | m0), x[2], y[2]);
                 ld2(psi + (i | m0 | m1), x[3], y[3]);
-                mv4(u, x);
-                mv4(u, y);
+                mv4<false>(u, x);
+                mv4<false>(u, y);
                 st2(psi + i, x[0], y[0]);
                 st2(psi + (i | m1), x[1], y[1]);
                 st2(psi + (i | m0), x[2], y[2]);
@@ -191,7 +191,7 @@ k_gate2(cx<R>* __restrict__ state, int64_t stride, int n, int q0, int q1, int ki
         const uint64_t i = insert0(insert0(w, qa), qb);
         cx<R> x[4];
         quad_load(psi, i, m0, m1, x);
-        mv4(u, x);
+        mv4<true>(u, x);
         quad_store(psi, i, m0, m1, x);
     }
 }
@@ -261,8 +261,8 @@ k_rev1(cx<R>* __restrict__ state, cx<R>* __restrict__ costate, int64_t stride, i
             else if (kind == K_RY) g += re_conj_mul(l1, a0) - re_conj_mul(l0, a1);
             else g += im_conj_mul(l0, a0) - im_conj_mul(l1, a1);   // RZ
         }
-        mv2(u, a0, a1);
-        mv2(u, l0, l1);
+        mv2<false>(u, a0, a1);
+        mv2<false>(u, l0, l1);
         psi[i0] = a0; psi[i1] = a1; lam[i0] = l0; lam[i1] = l1;
     }
     if (slot >= 0) {
@@ -305,7 +305,7 @@ k_rev2(cx<R>* __restrict__ state, cx<R>* __restrict__ costate, int64_t stride, i
                 G[1] += 2.0 * im_conj_mul(l[3], x[3]);
             }
         }
-        mv4(u, x);
+        mv4<false>(u, x);
         if (slot >= 0 && kind == K_U2) {
 #pragma unroll
             for (int a = 0; a < 4; ++a)
@@ -315,7 +315,7 @@ k_rev2(cx<R>* __restrict__ state, cx<R>* __restrict__ costate, int64_t stride, i
                     G[2 * (4 * a + c) + 1] += fma(double(l[a].im), double(x[c].re), -double(l[a].re) * double(x[c].im));
                 }
         }
-        mv4(u, l);
+        mv4<false>(u, l);
 #pragma unroll
         for (int a = 0; a < 4; ++a) { psi[idx[a]] = x[a]; lam[idx[a]] = l[a]; }
     }
@@ -505,7 +505,7 @@ k_gate_chunk_reg(cx<R>* __restrict__ state, int64_t stride, int n, ChunkMap map,
         gate_mat1<R>(kind, prm, p0, cm, mat, umat, inv != 0, u);
 #pragma unroll
         for (int i = 0; i < CF::RA; ++i)
-            if (!((i >> P0) & 1)) mv2(u, a[i], a[i | (1 << P0)]);
+            if (!((i >> P0) & 1)) mv2<true>(u, a[i], a[i | (1 << P0)]);
     } else {
         cx<R> u[16];
         gate_mat2<R>(kind, prm, p0, p1, cm, mat, umat, inv != 0, u);
@@ -514,7 +514,7 @@ k_gate_chunk_reg(cx<R>* __restrict__ state, int64_t stride, int n, ChunkMap map,
         for (int i = 0; i < CF::RA; ++i) {
             if ((i & M0) || (i & M1)) continue;
             cx<R> x[4] = {a[i], a[i | M1], a[i | M0], a[i | M0 | M1]};
-            mv4(u, x);
+            mv4<true>(u, x);
             a[i] = x[0];
             a[i | M1] = x[1];
             a[i | M0] = x[2];
@@ -562,7 +562,7 @@ k_gate_chunk_lds(cx<R>* __restrict__ state, int64_t stride, int n, ChunkMap map,
         for (int j = 0; j < (1 << CF::C) / 2 / NTHREADS; ++j) {
             const uint32_t i = uint32_t(insert0(uint64_t(j) * NTHREADS + t, lo));
             cx<R> x0 = lds[i], x1 = lds[i | m0];
-            mv2(u, x0, x1);
+            mv2<true>(u, x0, x1);
             lds[i] = x0;
             lds[i | m0] = x1;
         }
@@ -573,7 +573,7 @@ k_gate_chunk_lds(cx<R>* __restrict__ state, int64_t stride, int n, ChunkMap map,
         for (int j = 0; j < (1 << CF::C) / 4 / NTHREADS; ++j) {
             const uint32_t i = uint32_t(insert0(insert0(uint64_t(j) * NTHREADS + t, lo), hi));
             cx<R> x[4] = {lds[i], lds[i | m1], lds[i | m0], lds[i | m0 | m1]};
-            mv4(u, x);
+            mv4<true>(u, x);
             lds[i] = x[0];
             lds[i | m1] = x[1];
             lds[i | m0] = x[2];

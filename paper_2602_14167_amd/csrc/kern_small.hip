@@ -79,35 +79,13 @@ __device__ __forceinline__ void gate_sync(bool many) {
     }
 }
 
-// u x with the roundings written out: of the products of a sum, the one that is
-// rounded first (the compiler's own choice varies between copies of the
-// expression u x).  The imaginary part rounds u.im x.re first, or (SWAP) u.re x.im.
-template <bool SWAP, typename R>
-__device__ __forceinline__ cx<R> rmul(cx<R> u, cx<R> x) {
-    return {fmaR(u.re, x.re, -(u.im * x.im)),
-            SWAP ? fmaR(u.im, x.re, u.re * x.im) : fmaR(u.re, x.im, u.im * x.re)};
-}
-template <typename R>
-__device__ __forceinline__ void pair_mul(const cx<R>* u, cx<R>& a0, cx<R>& a1) {
-    const cx<R> x0 = a0, x1 = a1;
-    a0 = cfma(u[1], x1, rmul<false>(u[0], x0));
-    a1 = cfma(u[3], x1, rmul<false>(u[2], x0));
-}
-template <bool SWAP, typename R>
-__device__ __forceinline__ void quad_mul(const cx<R>* u, cx<R>* x) {
-    const cx<R> x0 = x[0], x1 = x[1], x2 = x[2], x3 = x[3];
-#pragma unroll
-    for (int a = 0; a < 4; ++a)
-        x[a] = cfma(u[4 * a + 3], x3, cfma(u[4 * a + 2], x2, cfma(u[4 * a + 1], x1, rmul<SWAP>(u[4 * a], x0))));
-}
-
 template <typename R>
 __device__ __forceinline__ cx<R> dag(const cx<R>* u, int dim, int a, int b, bool inv) {
     return inv ? conj(u[b * dim + a]) : u[a * dim + b];
 }
 
 // a two-qubit gate (or its inverse) on one quad; x: local index, q0 = most
-// significant; swap: the per-gate forward kernel's copy for single quads
+// significant; swap: the per-gate forward kernel's rounding of single quads (plaingate.h)
 template <typename R>
 __device__ __forceinline__ void quad_apply(int kind, const cx<R>* u, bool inv, bool swap, cx<R>* x) {
     if (kind == K_CNOT) {   // (exact either way: the dense product adds zeros)
@@ -120,8 +98,8 @@ __device__ __forceinline__ void quad_apply(int kind, const cx<R>* u, bool inv, b
         for (int a = 0; a < 4; ++a)
 #pragma unroll
             for (int b = 0; b < 4; ++b) m[4 * a + b] = dag(u, 4, a, b, inv);
-        if (swap) quad_mul<true>(m, x);
-        else quad_mul<false>(m, x);
+        if (swap) mv4<true>(m, x);
+        else mv4<false>(m, x);
     }
 }
 
@@ -296,7 +274,7 @@ __global__ void __launch_bounds__(SM_THREADS, PARTS == SM_PAULI ? 5 : 1) k_small
                     for (uint32_t w = t; w < pairs; w += T) {
                         const uint32_t i0 = insert_zero(w, q0);
                         cx<R> x0 = psi[i0], x1 = psi[i0 | b0];
-                        pair_mul(m, x0, x1);
+                        mv2<false>(m, x0, x1);
                         psi[i0] = x0;
                         psi[i0 | b0] = x1;
                     }
@@ -358,8 +336,8 @@ __global__ void __launch_bounds__(SM_THREADS, PARTS == SM_PAULI ? 5 : 1) k_small
                             else if (kind == K_RY) g0 += re_conj_mul(l1, x0) - re_conj_mul(l0, x1);
                             else g0 += im_conj_mul(l0, x0) - im_conj_mul(l1, x1);   // RZ
                         }
-                        pair_mul(m, x0, x1);
-                        pair_mul(m, l0, l1);
+                        mv2<false>(m, x0, x1);
+                        mv2<false>(m, l0, l1);
                         psi[i0] = x0;
                         psi[i0 | b0] = x1;
                         lam[i0] = l0;

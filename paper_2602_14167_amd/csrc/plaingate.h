@@ -44,18 +44,31 @@ __device__ __forceinline__ void gate_mat2(int kind, const R* prm, int p0, int p1
     if (inv) dagger_inplace<R, 4>(u);
 }
 
-template <typename R>
-__device__ __forceinline__ void mv2(const cx<R>* u, cx<R>& a0, cx<R>& a1) {
-    const cx<R> x0 = a0, x1 = a1;
-    a0 = cfma(u[1], x1, u[0] * x0);
-    a1 = cfma(u[3], x1, u[2] * x0);
+// Products with the roundings written out.  Left to the compiler, which of the two
+// products of a sum is rounded first varies between copies of u x, so that two kernels
+// that apply the same gate could differ, or change with the compiler.  u x: the real
+// part rounds u.im x.im first; the imaginary part u.im x.re, or with SWAP u.re x.im.
+// The chunked kernels take SWAP, and two-qubit gates on single quads (qubit 0, two
+// qubits in all, complex128) do; everything else takes the other.
+template <bool SWAP, typename R>
+__device__ __forceinline__ cx<R> rmul(cx<R> u, cx<R> x) {
+    return {fmaR(u.re, x.re, -(u.im * x.im)),
+            SWAP ? fmaR(u.im, x.re, u.re * x.im) : fmaR(u.re, x.im, u.im * x.re)};
 }
 
-template <typename R>
+template <bool SWAP, typename R>
+__device__ __forceinline__ void mv2(const cx<R>* u, cx<R>& a0, cx<R>& a1) {
+    const cx<R> x0 = a0, x1 = a1;
+    a0 = cfma(u[1], x1, rmul<SWAP>(u[0], x0));
+    a1 = cfma(u[3], x1, rmul<SWAP>(u[2], x0));
+}
+
+template <bool SWAP, typename R>
 __device__ __forceinline__ void mv4(const cx<R>* u, cx<R>* x) {
     const cx<R> x0 = x[0], x1 = x[1], x2 = x[2], x3 = x[3];
 #pragma unroll
-    for (int a = 0; a < 4; ++a) x[a] = cfma(u[4 * a + 3], x3, cfma(u[4 * a + 2], x2, cfma(u[4 * a + 1], x1, u[4 * a] * x0)));
+    for (int a = 0; a < 4; ++a)
+        x[a] = cfma(u[4 * a + 3], x3, cfma(u[4 * a + 2], x2, cfma(u[4 * a + 1], x1, rmul<SWAP>(u[4 * a], x0))));
 }
 
 }  // namespace tcng

@@ -51,6 +51,8 @@ KIND_NAME = {v: k for k, v in KIND.items()}
 KERNEL_SOURCES = {
     "tile": ["common.h", "devutil.h", "gates.h", "kernels.h", "kern_tile.hip", "plan.cpp", "plan.h"],
     "fused": ["common.h", "devutil.h", "gates.h", "kernels.h", "kern_fused.hip", "plan.cpp", "plan.h"],
+    "small": ["common.h", "devutil.h", "finish.h", "gates.h", "kernels.h", "kern_small.hip", "plaingate.h", "plan.cpp",
+              "plan.h"],
     "pauli": ["common.h", "devutil.h", "kernels.h", "kern_pauli.hip"],
     "plain": ["common.h", "devutil.h", "finish.h", "gates.h", "kernels.h", "kern_plain.hip", "plaingate.h"],
 }
@@ -77,7 +79,7 @@ def source_hash(kernel):
     h = hashlib.sha1()
     d = os.path.join(ROOT, "paper_2602_14167_amd", "csrc")
     group = ("fused" if kernel.startswith("fused") else "pauli" if kernel.startswith("pauli")
-             else "plain" if kernel.startswith("plain") else "tile")
+             else "plain" if kernel.startswith("plain") else "small" if kernel.startswith("small") else "tile")
     for f in KERNEL_SOURCES[group]:
         with open(os.path.join(d, f), "rb") as fh:
             h.update(fh.read())
@@ -92,7 +94,7 @@ def measured_traffic(workload_name, kernel):
     return rec[0]
 FAMILIES = ["fwd_tile", "rev_tile", "pauli_tile", "gate1", "gate2", "gatek", "rev1", "rev2", "pauli_group",
             "finish", "init", "fused_fwd", "fused_rev", "fused_grad", "mipt_hist", "mipt_decide", "mipt_collapse",
-            "pauli_coo", "shadow_sum", "shadow_pick", "qml"]
+            "pauli_coo", "shadow_sum", "shadow_pick", "qml", "small"]
 MFMA_F32_PEAK_TFLOPS = 157.3   # dense float32 matrix-core peak
 
 

@@ -331,8 +331,9 @@ size_t tcng_noalloc_scratch_bytes(void);
  *   14 trajectory histogram pass  15 trajectory decisions  16 trajectory collapse
  *   17 Pauli-sum COO entries  18 shadow chunk sums  19 shadow rotations and draws
  *   20 QML gate matrices, readout and angle gradients
+ *   21 small states: a whole forward sweep, Pauli sum or evaluation
  * tcng_profile_end stops recording and frees the events. */
-enum { TCNG_PROF_FAMILIES = 21 };
+enum { TCNG_PROF_FAMILIES = 22 };
 tcng_status tcng_profile_begin(int32_t max_launches);
 tcng_status tcng_profile_query(int32_t family, int32_t* launches, double* total_ms);
 tcng_status tcng_profile_end(void);

@@ -52,7 +52,8 @@ constexpr int MAX_QUBITS = 34;
 // ---------------------------------------------------------------------------
 enum Family { F_FWD_TILE, F_REV_TILE, F_PAULI_TILE, F_GATE1, F_GATE2, F_GATEK, F_REV1, F_REV2, F_PAULI_GROUP,
               F_FINISH, F_INIT, F_FUSED_FWD, F_FUSED_REV, F_FUSED_GRAD, F_MIPT_HIST, F_MIPT_DECIDE,
-              F_MIPT_COLLAPSE, F_PAULI_COO, F_SHADOW_SUM, F_SHADOW_PICK, F_QML, F_COUNT };
+              F_MIPT_COLLAPSE, F_PAULI_COO, F_SHADOW_SUM, F_SHADOW_PICK, F_QML, F_SMALL,
+              F_COUNT };
 static_assert(F_COUNT == TCNG_PROF_FAMILIES, "profiler families");
 
 struct Profiler {
@@ -717,8 +718,8 @@ SmallJob small_job(const tcng_circuit* c, const void* params, const tcng_pauli_s
     }
     return J;
 }
-tcng_status run_small(const SmallJob& J, const tcng_state* s, int family, hipStream_t st) {
-    PROF_TRY(family, s->dtype == TCNG_C64 ? launch_small<float>(J, s->batch, st) : launch_small<double>(J, s->batch, st));
+tcng_status run_small(const SmallJob& J, const tcng_state* s, hipStream_t st) {
+    PROF_TRY(F_SMALL, s->dtype == TCNG_C64 ? launch_small<float>(J, s->batch, st) : launch_small<double>(J, s->batch, st));
     return ok();
 }
 
@@ -1055,7 +1056,7 @@ tcng_status tcng_run_circuit(const tcng_circuit* c, const void* params, const tc
         return e ? e : ok();
     }
     if (use_small(mode, s->n_qubits, s->dtype))
-        return run_small(small_job(c, params, nullptr, s, nullptr, nullptr), s, F_FWD_TILE, st);
+        return run_small(small_job(c, params, nullptr, s, nullptr, nullptr), s, st);
     void* opm = tiled ? static_cast<char*>(ws) + L.opm_off : nullptr;
     const Job J = make_job(c, nullptr, s, nullptr, opm, nullptr, nullptr, L);
     tcng_status e;
@@ -1081,7 +1082,7 @@ tcng_status tcng_expect_pauli(const tcng_state* s, const tcng_pauli_sum* h, doub
     if (!ws || ws_bytes < L.total) return fail(TCNG_E_WORKSPACE, "workspace too small: need " + std::to_string(L.total));
     hipStream_t st = static_cast<hipStream_t>(stream);
     if (use_small(tmode, h->n, s->dtype))
-        return run_small(small_job(nullptr, nullptr, h, s, nullptr, out), s, F_PAULI_TILE, st);
+        return run_small(small_job(nullptr, nullptr, h, s, nullptr, out), s, st);
     double* epart = reinterpret_cast<double*>(static_cast<char*>(ws) + L.epart_off);
     const Job J = make_job(nullptr, h, s, nullptr, nullptr, nullptr, epart, L);
     tcng_status e = s->dtype == TCNG_C64 ? run_pauli<float, PAULI_RB>(h, s, nullptr, L, epart, mode, J, st)
@@ -1110,7 +1111,7 @@ tcng_status tcng_apply_pauli(const tcng_state* psi, const tcng_pauli_sum* h, con
     if (!ws || ws_bytes < L.total) return fail(TCNG_E_WORKSPACE, "workspace too small: need " + std::to_string(L.total));
     hipStream_t st = static_cast<hipStream_t>(stream);
     if (use_small(tmode, h->n, psi->dtype))
-        return run_small(small_job(nullptr, nullptr, h, psi, out->amps, energy), psi, F_PAULI_TILE, st);
+        return run_small(small_job(nullptr, nullptr, h, psi, out->amps, energy), psi, st);
     double* epart = reinterpret_cast<double*>(static_cast<char*>(ws) + L.epart_off);
     const Job J = make_job(nullptr, h, psi, out->amps, nullptr, nullptr, epart, L);
     tcng_status e = psi->dtype == TCNG_C64 ? run_pauli<float, PAULI_RB>(h, psi, out->amps, L, epart, mode, J, st)
@@ -1198,7 +1199,7 @@ tcng_status tcng_expect_grad(const tcng_circuit* c, const void* params, const tc
         S.grad = c->n_params ? grad : nullptr;
         S.gate_grad = gate_grad;
         S.do_rev = 1;
-        return run_small(S, psi, F_REV_TILE, st);
+        return run_small(S, psi, st);
     }
     const bool ctiled = use_tiled(mode, psi->n_qubits, dt);
     void* opm = ctiled ? w + L.opm_off : nullptr;

@@ -40,7 +40,11 @@ constexpr int HK = 8;                 // measured qubits per histogram round
 constexpr int HBINS = 1 << HK;
 constexpr int HCHUNK = 13;            // amplitudes per histogram workgroup: at most 2^13
 
-// the qubits member b measures in step s, from one load per lane (n <= 34 lanes;
+// index bits of a histogram workgroup's chunk (2^n / wgs amplitudes; 32 qubits are
+// allowed, so 2^n itself does not fit 32 bits)
+__host__ __device__ constexpr int chunk_bits(int n) { return n < HCHUNK ? n : HCHUNK; }
+
+// the qubits member b measures in step s, from one load per lane (n <= 32 lanes;
 // called by whole waves): a serial walk over the uniforms cost a load's
 // latency per qubit, 10 us of a 20-qubit decision
 __device__ __forceinline__ uint32_t measured_mask(const double* u, int64_t b, int n_steps, int s, int n, double p) {
@@ -77,7 +81,7 @@ __device__ __forceinline__ void hist_member(const float4* __restrict__ psi, int6
     const uint32_t M = round_mask(measured_mask(u, b, n_steps, s, n, p), r);
     if (!M) return;
     const uint32_t md = rec[(b * n_steps + s) * 2], bd = rec[(b * n_steps + s) * 2 + 1];
-    const uint32_t A = (1u << n) / uint32_t(wgs);   // amplitudes of the chunk (<= 2^HCHUNK)
+    const uint32_t A = 1u << chunk_bits(n);   // amplitudes of the chunk
     const uint32_t c0 = uint32_t(wg) * A;
     const float4* src = psi + b * stride4 + c0 / 2;
     // |psi_x|^2 of the chunk into LDS, zero where x contradicts the round's earlier
@@ -184,16 +188,17 @@ __device__ __forceinline__ void decide_member(const double* __restrict__ u, int 
     const uint32_t M = round_mask(all, r);
     if (!M) return;
     const int K = __popc(M);
-    const uint32_t A = (1u << n) / uint32_t(wgs);
+    const int cb = chunk_bits(n);
+    const uint32_t A = 1u << cb;
     const uint32_t mloc = M & (A - 1), mhigh = M & ~(A - 1);
     const int kloc = __popc(mloc);
     // bin g: low kloc bits from inside a chunk, the rest from the chunk's base; its
     // chunks w (the bits of w outside mhigh run free) in increasing order, 8
     // partials in flight (one at a time, a decision took 55 us at 20 qubits)
-    const uint32_t whigh = mhigh / A, wfree = (uint32_t(wgs) - 1u) & ~whigh;
+    const uint32_t whigh = mhigh >> cb, wfree = (uint32_t(wgs) - 1u) & ~whigh;
     const int nw = 1 << __popc(wfree);
     for (int g = lane; g < (1 << K); g += 64) {
-        const uint32_t lo = uint32_t(g) & ((1u << kloc) - 1), hi = deposit(uint32_t(g) >> kloc, mhigh) / A;
+        const uint32_t lo = uint32_t(g) & ((1u << kloc) - 1), hi = deposit(uint32_t(g) >> kloc, mhigh) >> cb;
         const double* src = part + (size_t(b) * wgs + hi) * HBINS + lo;
         double t = 0.0;
         uint32_t w = 0;   // the free bits, counted up through wfree
@@ -307,7 +312,7 @@ int mipt_wgs(int n) {
     return int(std::max<uint64_t>(1, std::min<uint64_t>(256, dim >> 13)));
 }
 
-int mipt_hist_wgs(int n) { return n > HCHUNK ? 1 << (n - HCHUNK) : 1; }
+int mipt_hist_wgs(int n) { return 1 << (n - chunk_bits(n)); }
 int mipt_rounds(int n) { return (n + HK - 1) / HK; }
 size_t mipt_hist_doubles(int n, int64_t batch) { return size_t(batch) * mipt_hist_wgs(n) * HBINS; }
 

@@ -1297,7 +1297,8 @@ __device__ __forceinline__ void coef_entry(const QStep* __restrict__ fsteps, int
     cx<R> ph = {R(1), R(0)};
 #pragma unroll
     for (int k = 0; k < QREG; ++k)
-        if (S.rz[k] >= 0) ph = ph * w[k];
+        if (S.rz[k] >= 0)   // (the roundings written out: they are those of all earlier results)
+            ph = {fmaR(ph.re, w[k].re, -(ph.im * w[k].im)), fmaR(ph.im, w[k].re, ph.re * w[k].im)};
     c[QPH + 2 * j] = ph.re;
     c[QPH + 2 * j + 1] = ph.im;
 }

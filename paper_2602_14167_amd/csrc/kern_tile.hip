@@ -80,7 +80,6 @@ struct V16<double> {
 
 struct PassInfo {
     int m, lo;
-    uint64_t tmask;
     int lq[MAX_TILE_BITS];   // local bit -> qubit (uniform: scalar registers)
 };
 
@@ -88,7 +87,6 @@ __device__ __forceinline__ PassInfo read_pass(cptr<Pass> P) {
     PassInfo pi;
     pi.m = P->m;
     pi.lo = P->lo;
-    pi.tmask = P->tile_mask;
 #pragma unroll
     for (int i = 0; i < MAX_TILE_BITS; ++i) pi.lq[i] = P->local_qubit[i];
     return pi;

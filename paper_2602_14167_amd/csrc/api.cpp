@@ -98,8 +98,13 @@ bool small_n(int n) { return n >= 2 && n <= SM_QUBITS; }
 // the small-state kernel serves the calls whose state is too small for the
 // tiled plans (a wave's 64 lanes beside the register bits): complex64 to 10
 // qubits, complex128 to 9.  It replaces one launch per gate and sweep.  At 10
-// qubits in complex128 the tiled pass stays: it takes about 100 us for one
-// parameter set and gains on larger batches.
+// qubits in complex128 the tiled passes stay.  Gradients there, tiled / small, in us:
+//   RY-RZ-CNOT ansatz, 4 layers:   1 set 79 / 157,   512 sets 107 / 208, 2048 sets 354 / 793
+//   RZZ and RX, 80 gates:          1 set 136 / 141,  512 sets 177 / 191, 2048 sets 659 / 724
+//   fSim, 80 gates:                1 set 166 / 169,  512 sets 222 / 229, 2048 sets 827 / 860
+//   80 gates of every kind:        1 set 192 / 121,  512 sets 254 / 164, 2048 sets 942 / 518
+// (rotation rounds take several gates per LDS round trip, the small kernel one; only
+// dense gates in the generic passes are slower than it).
 bool use_small(int mode, int n, int dtype) { return mode == TCNG_MODE_TILED && small_n(n) && !tiled_ok(n, dtype); }
 bool config_ok(const TileConfig& c, int dtype) {
     const int mmax = dtype == TCNG_C64 ? 13 : 12;

@@ -46,7 +46,7 @@ KIND_NAME = {v: k for k, v in KIND.items()}
 
 # HBM bytes per launch measured with rocprofv3 counters (FETCH_SIZE and
 # WRITE_SIZE in separate runs, scaled by what each reads for a 2 GiB device
-# copy: x1.99993 and x1.0), keyed by workload and kernel family, valid only
+# copy: x1.99994 and x1.0), keyed by workload and kernel family, valid only
 # for the kernel sources they were taken with (hash below).
 KERNEL_SOURCES = {
     "tile": ["common.h", "devutil.h", "gates.h", "kernels.h", "kern_tile.hip", "plan.cpp", "plan.h"],
@@ -57,20 +57,20 @@ KERNEL_SOURCES = {
     "plain": ["common.h", "devutil.h", "finish.h", "gates.h", "kernels.h", "kern_plain.hip", "plaingate.h"],
 }
 TRAFFIC = {
-    ("hea_n28_L12_tfim", "rev_tile"): (8.6047e+09, "34cae1f9856ca791"),
-    ("hea_n28_L12_tfim", "fwd_tile"): (4.2952e+09, "34cae1f9856ca791"),
-    ("hea_n28_L12_tfim", "fused_rev"): (8.7870e+09, "e6701c5affaf0dc5"),
-    ("hea_n28_L12_tfim", "fused_fwd"): (4.2968e+09, "e6701c5affaf0dc5"),
-    ("fsim_brickwork_n32_d20_tfim2d", "rev_tile"): (1.3745e+11, "34cae1f9856ca791"),
-    ("fsim_brickwork_n32_d20_tfim2d", "fwd_tile"): (6.8719e+10, "34cae1f9856ca791"),
-    ("mipt_haar_n20_d40_b1000_p0.2", "fused_fwd"): (1.6976e+10, "e6701c5affaf0dc5"),
-    ("qml_mnist_n10_l40_b15000", "fused_rev"): (5.0972e+08, "e6701c5affaf0dc5"),
-    ("qml_mnist_n10_l40_b15000", "fused_fwd"): (2.4651e+08, "e6701c5affaf0dc5"),
-    ("qml_cifar100_n12_l30_b5000", "fused_rev"): (6.7451e+08, "e6701c5affaf0dc5"),
-    ("qml_cifar100_n12_l30_b5000", "fused_fwd"): (3.2845e+08, "e6701c5affaf0dc5"),
-    ("haar_brickwork_uneven_1024", "fused_rev"): (1.5136e+10, "e6701c5affaf0dc5"),
-    ("tfim_coo_n24", "pauli_coo"): (1.3422e+10, "ba2bf1c0385a9695"),
-    ("single_gate_sweep_n30_c64", "plain_gate"): (1.7186e+10, "9295abc6ba4265a5"),
+    ("hea_n28_L12_tfim", "rev_tile"): (8.6052e+09, "4f3d200e886db60c"),
+    ("hea_n28_L12_tfim", "fwd_tile"): (4.2952e+09, "4f3d200e886db60c"),
+    ("hea_n28_L12_tfim", "fused_rev"): (8.7807e+09, "a8140b31ea5835f6"),
+    ("hea_n28_L12_tfim", "fused_fwd"): (4.2953e+09, "a8140b31ea5835f6"),
+    ("fsim_brickwork_n32_d20_tfim2d", "rev_tile"): (1.3745e+11, "4f3d200e886db60c"),
+    ("fsim_brickwork_n32_d20_tfim2d", "fwd_tile"): (6.8719e+10, "4f3d200e886db60c"),
+    ("mipt_haar_n20_d40_b1000_p0.2", "fused_fwd"): (1.7163e+10, "a8140b31ea5835f6"),
+    ("qml_mnist_n10_l40_b15000", "fused_rev"): (5.0946e+08, "a8140b31ea5835f6"),
+    ("qml_mnist_n10_l40_b15000", "fused_fwd"): (2.4628e+08, "a8140b31ea5835f6"),
+    ("qml_cifar100_n12_l30_b5000", "fused_rev"): (6.7386e+08, "a8140b31ea5835f6"),
+    ("qml_cifar100_n12_l30_b5000", "fused_fwd"): (3.2821e+08, "a8140b31ea5835f6"),
+    ("haar_brickwork_uneven_1024", "fused_rev"): (1.5143e+10, "a8140b31ea5835f6"),
+    ("tfim_coo_n24", "pauli_coo"): (1.3422e+10, "959dcc90423c9f95"),
+    ("single_gate_sweep_n30_c64", "plain_gate"): (1.7186e+10, "75c5c8d6a4292ce9"),
 }
 
 
@@ -978,6 +978,8 @@ def main():
         nbytes = algorithmic_bytes(dom, n, s, B, 0)
         roofline = roofline_entry(dom, flops, nbytes, fam_stats[dom]["avg_ms"])
         roofline["traffic"] = measured_traffic(w["name"], dom) if args.dtype == "c64" else None
+    elif "small" in fam_stats:
+        roofline = {"bound": "latency", "kernel": "small", "note": "one launch: a serial chain of gates per parameter set"}
     elif fam_stats:
         dom = max(fam_stats, key=lambda k: fam_stats[k]["total_ms"])
         roofline = {"bound": "hbm", "kernel": dom, "note": "plain per-gate path"}
